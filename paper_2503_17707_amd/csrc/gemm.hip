@@ -274,6 +274,161 @@ void gemm_kernel(GemmParams p, SplitArgs sa) {
     store_tile<T, EPI, MF, NF>(p, jb, m0 + wm * WM, n0 + wn * WN, lr, lg, acc);
 }
 
+// ---- few rows (batched decode, short prompts): wide-row weight streaming ------
+// One block computes all (at most BM) tokens x BN output features over one K
+// range; its waves split the features (and the tokens when WGM > 1).  A ring
+// stage holds BKE (128 or 256) K elements of the BM token rows and BN weight
+// rows, so a copy instruction fetches whole 256- or 512-byte row pieces; the
+// 128-byte pieces of the tiles above reach 3.5 TB/s on such products, these
+// 4.9 (N 16384, K 4096, 32 rows: 27.4 us against 37.3; N 2048, K 8192: 8.7
+// and a reduce against 16.6).  HBM-bound for large N, by its fixed ~3 us for
+// small ones.  The base K range of every wave is independent of the LoRA
+// segment (B = 0 stays bit-identical to the base), whose few columns are read
+// straight into registers: the first 64, requested ahead of the ring, have
+// landed by the time the base is done.
+template <typename T, int EPI, int BM, int BN, int WGM, int WGN, int BKE, int S, int ROLE>
+__global__ __launch_bounds__(64 * WGM * WGN) void stream_kernel(GemmParams p, SplitArgs sa) {
+    typedef typename Mfma<T>::vec8 vec8;
+    constexpr int NW = WGM * WGN;
+    constexpr int WM = BM / WGM, WN = BN / WGN;
+    constexpr int MF = WM / 16, NF = WN / 16;
+    constexpr int RB = BKE * 2;                // bytes per LDS row
+    constexpr int CPR = RB / 16;               // 16-byte chunks per row
+    constexpr int RPI = 1024 / RB;             // rows per copy instruction
+    constexpr int NL = (BM + BN) / RPI / NW;   // copy instructions per wave per stage
+    constexpr int STAGE = (BM + BN) * RB;
+    static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0, "copy slots split into X and W");
+    static_assert(S >= 2 && (S - 2) * NL < 64, "pipeline depth");
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave % WGM, wn = wave / WGM;
+    const int lr = lane & 15, lg = lane >> 4;
+    const int nbn = p.N / BN;
+    const int split = (int)blockIdx.x / nbn, n0 = ((int)blockIdx.x % nbn) * BN;
+    const int nk = p.K1 / BKE;
+    const int t0 = stream_stage(nk, split, sa.splits), n = stream_stage(nk, split + 1, sa.splits) - t0;
+
+    // copy j of this wave fills rows RPI (wave + NW j) .. of a stage, tokens
+    // first; the 16-byte chunks of a row are XOR-permuted by its low row bits
+    // (all 16 rows of an operand read then hit distinct banks)
+    uint32_t off[NL];
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+        const int row = (wave + NW * j) * RPI + lane / CPR;
+        const int ch = (lane % CPR) ^ (row & 15);
+        off[j] = (wave + NW * j) * RPI < BM
+                     ? ((uint32_t)min(row, p.M - 1) * (uint32_t)p.ldx + ch * 8) * 2
+                     : ((uint32_t)(n0 + row - BM) * (uint32_t)p.ldw + ch * 8) * 2;
+    }
+    const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
+    auto issue = [&](int t, int stage) {
+        const int64_t kb = (int64_t)t * RB;
+        const char* xk = (const char*)p.X + kb;
+        const char* wk = (const char*)p.W + kb;
+#pragma unroll
+        for (int j = 0; j < NL; ++j) {
+            const int I = wave + NW * j;
+            dma16s(I * RPI < BM ? xk : wk, off[j], lds0 + stage * STAGE + I * 1024);
+        }
+    };
+
+    f32x4 acc[NF][MF];
+#pragma unroll
+    for (int i = 0; i < NF; ++i)
+#pragma unroll
+        for (int j = 0; j < MF; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto compute = [&](int stage) {
+        const uint8_t* s = smem + stage * STAGE;
+#pragma unroll
+        for (int kk = 0; kk < BKE / 32; ++kk) {
+            const int ch = kk * 4 + lg;
+            vec8 b[MF];
+#pragma unroll
+            for (int j = 0; j < MF; ++j) {
+                const int row = wm * WM + j * 16 + lr;
+                b[j] = as_vec8<T>(*(const u32x4*)(s + row * RB + ((ch ^ (row & 15)) << 4)));
+            }
+#pragma unroll
+            for (int i = 0; i < NF; ++i) {
+                const int row = BM + wn * WN + i * 16 + lr;
+                const vec8 a = as_vec8<T>(*(const u32x4*)(s + row * RB + ((ch ^ (row & 15)) << 4)));
+#pragma unroll
+                for (int j = 0; j < MF; ++j) acc[i][j] = Mfma<T>::mma(a, b[j], acc[i][j]);
+            }
+        }
+    };
+
+    // LoRA segment of this block's output group (last split): operands of one
+    // 32-wide step straight from global memory
+    int nk2 = 0;
+    const T* X2 = (const T*)p.X2;
+    if (p.K2 > 0 && split == sa.splits - 1) {
+        const int g = n0 / p.group;  // the group size is a multiple of BN
+        if ((p.k2_mask >> g) & 1u) {
+            nk2 = p.K2 / 32;
+            X2 += (int64_t)g * p.x2_group_stride;
+        }
+    }
+    struct Ops {
+        u32x4 w[NF], x[MF];
+    };
+    auto load2 = [&](Ops& o, int t) {
+#pragma unroll
+        for (int i = 0; i < NF; ++i)
+            o.w[i] = *(const u32x4*)((const T*)p.W2 + (int64_t)(n0 + wn * WN + i * 16 + lr) * p.ldw2 + t * 32 + 8 * lg);
+#pragma unroll
+        for (int j = 0; j < MF; ++j)
+            o.x[j] = *(const u32x4*)(X2 + (int64_t)min(wm * WM + j * 16 + lr, p.M - 1) * p.ldx2 + t * 32 + 8 * lg);
+    };
+    auto mul2 = [&](const Ops& o) {
+#pragma unroll
+        for (int i = 0; i < NF; ++i)
+#pragma unroll
+            for (int j = 0; j < MF; ++j) acc[i][j] = Mfma<T>::mma(as_vec8<T>(o.w[i]), as_vec8<T>(o.x[j]), acc[i][j]);
+    };
+    Ops l0, l1;
+    if (nk2 > 0) {  // K2 is a multiple of 64: at least two steps
+        load2(l0, 0);
+        load2(l1, 1);
+    }
+
+#pragma unroll
+    for (int q = 0; q < S - 1; ++q)
+        if (q < n) issue(t0 + q, q);
+    int t = 0, st = 0;
+    for (; t + S - 1 < n; ++t) {
+        wait_vmcnt<(S - 2) * NL>();
+        __syncthreads();  // stage st visible to all waves; the stage before it free
+        issue(t0 + t + S - 1, st == 0 ? S - 1 : st - 1);
+        compute(st);
+        st = st == S - 1 ? 0 : st + 1;
+    }
+    for (; t < n; ++t) {
+        wait_vmcnt<0>();
+        __syncthreads();
+        compute(st);
+        st = st == S - 1 ? 0 : st + 1;
+    }
+    if (nk2 > 0) {
+        mul2(l0);
+        mul2(l1);
+        for (int q = 2; q < nk2; q += 2) {
+            load2(l0, q);
+            load2(l1, q + 1);
+            mul2(l0);
+            mul2(l1);
+        }
+    }
+    TileJob jb;
+    jb.partial = sa.splits > 1;
+    jb.pbase = sa.ws + (int64_t)split * p.M * p.N;
+    jb.ldp = p.N;
+    jb.om = jb.on = 0;
+    store_tile<T, EPI, MF, NF>(p, jb, wm * WM, n0 + wn * WN, lr, lg, acc);
+}
+
 // Sum the split-K partials in split order, then apply the epilogue.
 template <typename T, int EPI, int ROLE>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmParams p, SplitArgs sa) {
@@ -393,11 +548,17 @@ hipError_t launch_resid_ln(const GemmParams& p, const SplitArgs& sa, hipStream_t
     // occupancy hides the latency and registers matter more
     if (p.N <= 2048) {
         if (sa.splits == 2) PB_RLN(2, 2);
+        else if (sa.splits == 3) PB_RLN(2, 3);
         else if (sa.splits == 4) PB_RLN(2, 4);
+        else if (sa.splits == 6) PB_RLN(2, 6);
+        else if (sa.splits == 8) PB_RLN(2, 8);
         else PB_RLN(2, 0);
     } else if (p.N <= 4096) {
         if (sa.splits == 2) PB_RLN(4, 2);
+        else if (sa.splits == 3) PB_RLN(4, 3);
         else if (sa.splits == 4) PB_RLN(4, 4);
+        else if (sa.splits == 6) PB_RLN(4, 6);
+        else if (sa.splits == 8) PB_RLN(4, 8);
         else PB_RLN(4, 0);
     } else if (p.N <= 8192) {
         PB_RLN(8, 0);
@@ -447,8 +608,40 @@ hipError_t launch_cfg(const GemmParams& p, const GemmWorkspace& wsp, int splits,
     return finish_split<T, EPI, ROLE>(p, sa, s);
 }
 
+template <typename T, int EPI, int BM, int BN, int WGM, int WGN, int BKE, int S, int ROLE>
+hipError_t launch_stream_cfg(const GemmParams& p, const GemmWorkspace& wsp, int splits, hipStream_t s) {
+    constexpr int LDS = S * (BM + BN) * BKE * 2;
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void*)stream_kernel<T, EPI, BM, BN, WGM, WGN, BKE, S, ROLE>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    SplitArgs sa{};
+    sa.splits = splits;
+    sa.ws = (float*)wsp.ws;
+    PB_LAUNCH((stream_kernel<T, EPI, BM, BN, WGM, WGN, BKE, S, ROLE>), dim3(p.N / BN * splits),
+              dim3(64 * WGM * WGN), LDS, s, p, sa);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || splits == 1) return e;
+    return finish_split<T, EPI, ROLE>(p, sa, s);
+}
+
+template <typename T, int EPI, int ROLE>
+hipError_t launch_stream(const GemmParams& p, const GemmWorkspace& wsp, const StreamPlan& sp, hipStream_t s) {
+    if (sp.bm == 64) return launch_stream_cfg<T, EPI, 64, 64, 1, 4, 128, 4, ROLE>(p, wsp, sp.splits, s);
+    if (sp.bn == 32) return launch_stream_cfg<T, EPI, 32, 32, 1, 2, 128, 4, ROLE>(p, wsp, sp.splits, s);
+    if (sp.bk == 256) return launch_stream_cfg<T, EPI, 32, 64, 1, 4, 256, 3, ROLE>(p, wsp, sp.splits, s);
+    return launch_stream_cfg<T, EPI, 32, 64, 1, 4, 128, 3, ROLE>(p, wsp, sp.splits, s);
+}
+
 template <typename T, int EPI, int ROLE>
 hipError_t launch_tiles(const GemmParams& p, const GemmWorkspace& wsp, hipStream_t s) {
+    if constexpr (ROLE != 4) {
+        const StreamPlan sp = plan_stream(p, wsp);
+        if (sp.bm) return launch_stream<T, EPI, ROLE>(p, wsp, sp, s);
+    }
     const TilePlan tp = plan_for_role(ROLE, p, wsp);
     if constexpr (ROLE == 4) {
         return launch_cfg<T, EPI, 64, 64, 2, 2, 4, 4>(p, wsp, tp.splits, 0, s);
@@ -617,7 +810,12 @@ hipError_t launch_gemm(int dtype, int role, int epi, const GemmParams& p, const 
         return hipErrorInvalidValue;
     const int expect[5] = {EPI_QKV, EPI_RESID, EPI_RELU, EPI_RESID, EPI_SHRINK};
     if (role < 0 || role > 4 || expect[role] != epi) return hipErrorInvalidValue;
-    if (p.M <= GEMV_MAX_ROWS && PB_GEMM_GEMV)
+    // The GEMV's fp32 dot products cost arithmetic per row (N 8192, K 2048: 7.6
+    // us for 1 row, 13.2 for 4, 22.8 for 8), the wide-row streaming kernel's
+    // matrix products do not (8-10 us up to 32 rows): the GEMV takes 1 and 2
+    // rows, and up to 8 where that kernel does not apply (the LoRA shrink, K
+    // not a multiple of 128).
+    if (PB_GEMM_GEMV && (p.M <= 2 || (p.M <= GEMV_MAX_ROWS && (role == 4 || !plan_stream(p, wsp).bm))))
         return dtype == 1 ? launch_gemv_typed<_Float16>(role, p, s) : launch_gemv_typed<__bf16>(role, p, s);
     if (dtype == 1) return launch_typed<_Float16>(role, p, wsp, s);
     return launch_typed<__bf16>(role, p, wsp, s);

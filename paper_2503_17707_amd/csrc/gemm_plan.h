@@ -231,6 +231,57 @@ TilePlan plan_tiles(const GemmParams& p, const GemmWorkspace& wsp) {
     return best;
 }
 
+// Few token rows (more than the GEMV takes, at most STREAM_MAX_ROWS): the
+// weights are streamed through a ring of wide LDS rows (128 or 256 K elements
+// per row), one block of all tokens x `bn` output features per K range.
+constexpr int STREAM_MAX_ROWS = 64;
+
+struct StreamPlan {
+    int bm;      // tokens per block (32 or 64); 0: not a stream launch
+    int bn;      // output features per block (64 or 32)
+    int bk;      // K elements per ring stage (128 or 256)
+    int splits;  // K ranges
+};
+
+// K ranges of a stream launch: `splits` nearly equal runs of K stages
+// (split s takes stages [nk s / splits, nk (s + 1) / splits)).
+__host__ __device__ __forceinline__ int stream_stage(int nk, int split, int splits) {
+    return (int)((int64_t)nk * split / splits);
+}
+
+// Block shape and K split of a stream launch.  Measured on gfx950: one CU
+// copies ~45 GB/s into LDS whatever the block shape, the chip streams cold
+// weights at ~5.2 TB/s, a launch costs ~3 us beside that, a separate reduce
+// of split partials ~4 us; where a LayerNorm follows (ln_out) the reduce is
+// that LayerNorm's own pass and a split costs only its partials' reads.  The
+// model below is within 15% of the measured times over M = 16 .. 64, N = 2048
+// .. 16384, K = 2048 .. 16384.  K not a multiple of 128 is left to the tiles.
+StreamPlan plan_stream(const GemmParams& p, const GemmWorkspace& wsp) {
+    StreamPlan best{0, 0, 0, 1};
+    if (p.M > STREAM_MAX_ROWS || p.K1 % 128) return best;
+    const int bm = p.M <= 32 ? 32 : 64;
+    const double floor_t = (double)p.N * p.K1 * 2 / 5.2e12;
+    double best_t = 1e30;
+    for (int bn : {64, 32}) {
+        if (bm == 64 && bn == 32) continue;
+        for (int s : {1, 2, 3, 4, 6, 8}) {
+            if (s > 1 && (p.K1 / 128 / s < 4 || !wsp.ws || (double)p.M * p.N * 4 * s > (double)wsp.bytes)) break;
+            const long per_cu = ((long)(p.N / bn) * s + 255) / 256;  // blocks of the busiest CU
+            const double copy_t = per_cu * ((double)p.K1 / s) * (bm + bn) * 2 / 45e9;
+            double t = std::max(copy_t, floor_t);
+            if (s > 1) t += p.ln_out ? 0.3e-6 * s : 4e-6;
+            if (t < best_t * 0.98) {  // the simpler plan on near ties
+                best_t = t;
+                best = {bm, bn, 128, s};
+            }
+        }
+    }
+    // unsplit with a block or so per CU: 512-byte rows (144 KB of ring, one
+    // block per CU) measured 6-8% faster than 256-byte rows
+    if (best.bm == 32 && best.bn == 64 && best.splits == 1 && p.K1 % 256 == 0) best.bk = 256;
+    return best;
+}
+
 // Tile plan of a launch by role: the projections by the cost model above,
 // the LoRA shrink (role 4) always 64 x 64, split along K when few.
 TilePlan plan_for_role(int role, const GemmParams& p, const GemmWorkspace& wsp) {

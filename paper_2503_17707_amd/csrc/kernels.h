@@ -53,7 +53,7 @@ struct GemmWorkspace {
     size_t bytes;
 };
 
-// Products with at most this many token rows stream the weights with the
+// Products with at most this many token rows may stream the weights with the
 // GEMV kernel (decode steps) instead of MFMA tiles.
 constexpr int GEMV_MAX_ROWS = 8;
 
