@@ -99,9 +99,18 @@ int lm_head_blocks(int V);
 hipError_t launch_lm_head(int dtype, const float* z, int B, const void* E, int V, int d,
                           float* logits, float* pval, int* pidx, hipStream_t s);
 
+// The same for several sequences on the matrix units (lmhead.hip), with
+// lm_head_mfma_blocks(V) partials per sequence; d a multiple of 128, V d below
+// 2^31; scratch of lm_head_mfma_scratch(d) bytes, 16-byte aligned.
+bool lm_head_use_mfma(int B, int V, int d);  // the faster one for this call
+int lm_head_mfma_blocks(int V);
+size_t lm_head_mfma_scratch(int d);
+hipError_t launch_lm_head_mfma(int dtype, const float* z, int B, const void* E, int V, int d, float* logits,
+                               float* pval, int* pidx, void* scratch, hipStream_t s);
+
 // tok[b] = lowest index of the maximum of logits[b, :], from the LM head's
-// partials (-1 if no finite maximum exists).
-hipError_t launch_argmax(const float* pval, const int* pidx, int B, int V, int32_t* tok,
+// nblk partials per sequence (-1 if no finite maximum exists).
+hipError_t launch_argmax(const float* pval, const int* pidx, int B, int nblk, int32_t* tok,
                          hipStream_t s);
 
 // Scatter one adapter's staged LoRA blobs (per layer: A_t [r, d], B_t [d, r] for

@@ -465,11 +465,10 @@ hipError_t launch_lm_head(int dtype, const float* z, int B, const void* E, int V
     return hipSuccess;
 }
 
-hipError_t launch_argmax(const float* pval, const int* pidx, int B, int V, int32_t* tok,
+hipError_t launch_argmax(const float* pval, const int* pidx, int B, int nblk, int32_t* tok,
                          hipStream_t s) {
     if (B <= 0) return hipSuccess;
-    PB_LAUNCH(argmax_final_kernel, dim3(B), dim3(256), 0, s, pval, pidx,
-                       lm_head_blocks(V), tok);
+    PB_LAUNCH(argmax_final_kernel, dim3(B), dim3(256), 0, s, pval, pidx, nblk, tok);
     return hipGetLastError();
 }
 

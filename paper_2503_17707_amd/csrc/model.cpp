@@ -225,8 +225,9 @@ ArenaLayout arena_layout(const pb_config* c) {
     a.zf = take(B * d * 4);
     a.logits = take(B * V * 4);
     a.outtok = take(B * 4);
-    a.pval = take(B * (size_t)pb::lm_head_blocks((int)V) * 4);
-    a.pidx = take(B * (size_t)pb::lm_head_blocks((int)V) * 4);
+    const size_t parts = std::max(pb::lm_head_blocks((int)V), pb::lm_head_mfma_blocks((int)V));
+    a.pval = take(B * parts * 4);
+    a.pidx = take(B * parts * 4);
     a.staging_bytes = c->max_adapters > 0 ? L * lora_layer_elems(c, c->max_rank, 0xF) * 2 : 0;
     a.staging = take(a.staging_bytes);
     // KV cache for decoding: [L][max_batch][max_pos][k | v] (dt)
@@ -1051,14 +1052,23 @@ int enqueue_forward(pb_model* m, int B, int T, bool use_lora, uint32_t lora_unio
         HIP_TRY(pb::launch_layernorm(dt, x, T, T - 1, m->gtensor(PB_G_LNF_G), m->gtensor(PB_G_LNF_B), zf,
                                      true, B, d, c.ln_eps, s));
     }
+    // the split-K workspace is free here; it holds the terms of zf
+    const bool head_mfma =
+        pb::lm_head_use_mfma(B, c.vocab, d) && pb::lm_head_mfma_scratch(d) <= a.ws_bytes;
     {
         Timed t(m, PB_K_LM_HEAD);
-        HIP_TRY(pb::launch_lm_head(dt, zf, B, m->gtensor(PB_G_EMBED), c.vocab, d,
-                                   (float*)m->at(a.logits), (float*)m->at(a.pval), (int*)m->at(a.pidx), s));
+        float* lg = (float*)m->at(a.logits);
+        float* pv = (float*)m->at(a.pval);
+        int* pi = (int*)m->at(a.pidx);
+        if (head_mfma)
+            HIP_TRY(pb::launch_lm_head_mfma(dt, zf, B, m->gtensor(PB_G_EMBED), c.vocab, d, lg, pv, pi, m->at(a.ws), s));
+        else
+            HIP_TRY(pb::launch_lm_head(dt, zf, B, m->gtensor(PB_G_EMBED), c.vocab, d, lg, pv, pi, s));
     }
     {
         Timed t(m, PB_K_ARGMAX);
-        HIP_TRY(pb::launch_argmax((const float*)m->at(a.pval), (const int*)m->at(a.pidx), B, c.vocab,
+        HIP_TRY(pb::launch_argmax((const float*)m->at(a.pval), (const int*)m->at(a.pidx), B,
+                                  head_mfma ? pb::lm_head_mfma_blocks(c.vocab) : pb::lm_head_blocks(c.vocab),
                                   (int32_t*)m->at(a.outtok), s));
     }
     return PB_OK;
