@@ -117,12 +117,23 @@ hipError_t launch_argmax(const float* pval, const int* pidx, int B, int nblk, in
 // the targets in mask) into slot `slot` of the packed per-layer arrays
 // Acat [L][4][kw][d] and Bcat [L][4][d][kw] (slot columns slot*rs .. +rs),
 // zero-filling ranks r..rs-1 and absent targets.
-// W [d, d] += scale * (slot's B [d, rs]) (slot's A [rs, d]), rounded once (misc.hip).
-hipError_t launch_lora_merge(int dtype, void* W, const void* Acat, const void* Bcat, int d, int kw, int rs,
-                             int slot, float scale, hipStream_t s);
-
 hipError_t launch_lora_pack(int dtype, const void* staging, size_t staging_layer_elems, int L,
                             int d, int r, uint32_t mask, int slot, int rs, int kw, void* Acat,
                             void* Bcat, hipStream_t s);
+
+// Attention weights of every layer, [Wq|Wk|Wv|Wo] as four [d, d] matrices at
+// src + layer * src_stride (bytes), written to dst + layer * dst_stride (the
+// same place allowed): targets in merge_mask as dt(src + scale * (slot's B [d,
+// rs]) (slot's A [rs, d])), rounded once, targets in copy_mask unchanged, the
+// others not written (misc.hip).  A, B: the packed slot arrays of all layers.
+struct MergeParams {
+    const char* src; int64_t src_stride;
+    char* dst; int64_t dst_stride;
+    const void* A; const void* B;
+    int layers, d, kw, rs, slot;
+    float scale;
+    uint32_t merge_mask, copy_mask;
+};
+hipError_t launch_lora_merge(int dtype, const MergeParams& p, hipStream_t s);
 
 }  // namespace pb

@@ -322,38 +322,60 @@ __global__ __launch_bounds__(256) void lora_pack_kernel(const T* __restrict__ st
 }
 
 
-// ---- merged LoRA: W_t += s * B_t A_t in place ------------------------------
-// Thread (row n, columns 8c .. 8c+7) of target weight W [d, d]: the rank-rs
-// product of the slot's B rows (Bcat [d][kw], columns slot*rs ..) and A
-// columns (Acat [kw][d], rows slot*rs ..) in fp32, ranks in order, then one
-// rounding of W + s * product to dt.
+// ---- merged LoRA: W_t = src_t + s * B_t A_t for every layer and target -------
+// One launch covers all layers and the targets of `merge_mask` (merged) and
+// `copy_mask` (src copied unchanged: an adapter switch restoring a target that
+// only the previous adapter changed).  A thread holds 8 columns of MERGE_ROWS
+// rows of one matrix: the slot's A columns (Acat [kw][d], rows slot*rs ..) are
+// read once for all of its rows, whose B values (Bcat [d][kw], columns slot*rs
+// ..) are the same for the whole block.  The rank-rs product is summed in
+// fp32, ranks in order, then W + s * product is rounded once to dt.  HBM-bound:
+// src read, W written (one row per thread re-read A from L2 for every row and
+// took 12.2 us per 2048 x 2048 matrix, 1.4 TB/s; 805 MB of an OPT-1.3B switch
+// took 586 us plus 293 for the restoring copy).
+constexpr int MERGE_ROWS = 8;
+
 template <typename T>
-__global__ __launch_bounds__(256) void lora_merge_kernel(T* __restrict__ W, const T* __restrict__ Acat,
-                                                        const T* __restrict__ Bcat, int d, int kw,
-                                                        int rs, int slot, float scale) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int per_row = d / 8;
-    if (i >= (int64_t)d * per_row) return;
-    const int n = (int)(i / per_row), c = (int)(i % per_row) * 8;
-    float acc[8] = {};
-    const T* brow = Bcat + (int64_t)n * kw + (int64_t)slot * rs;
-    for (int j = 0; j < rs; ++j) {
-        const float b = (float)brow[j];
-        const u32x4 araw = *(const u32x4*)(Acat + ((int64_t)slot * rs + j) * d + c);
-        T a[8];
-        __builtin_memcpy(a, &araw, 16);
+__global__ __launch_bounds__(256) void lora_merge_kernel(MergeParams p) {
+    const int d = p.d;
+    const int c = ((int)blockIdx.x * 256 + (int)threadIdx.x) * 8;
+    if (c >= d) return;
+    const int n0 = (int)blockIdx.y * MERGE_ROWS;
+    const int l = (int)blockIdx.z >> 2, t = (int)blockIdx.z & 3;
+    const bool merge = (p.merge_mask >> t) & 1u;
+    if (!merge && !((p.copy_mask >> t) & 1u)) return;
+    const int64_t at = ((int64_t)t * d + n0) * d + c;
+    const T* src = (const T*)(p.src + (int64_t)l * p.src_stride) + at;
+    T* dst = (T*)(p.dst + (int64_t)l * p.dst_stride) + at;
+    u32x4 raw[MERGE_ROWS];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] += b * (float)a[e];
+    for (int r = 0; r < MERGE_ROWS; ++r) raw[r] = *(const u32x4*)(src + (int64_t)r * d);
+    if (merge) {
+        const T* A = (const T*)p.A + ((int64_t)(l * 4 + t) * p.kw + (int64_t)p.slot * p.rs) * d + c;
+        const T* B = (const T*)p.B + ((int64_t)(l * 4 + t) * d + n0) * p.kw + (int64_t)p.slot * p.rs;
+        float acc[MERGE_ROWS][8] = {};
+        for (int j = 0; j < p.rs; ++j) {
+            const u32x4 araw = *(const u32x4*)(A + (int64_t)j * d);
+            T a[8];
+            __builtin_memcpy(a, &araw, 16);
+#pragma unroll
+            for (int r = 0; r < MERGE_ROWS; ++r) {
+                const float b = (float)B[(int64_t)r * p.kw + j];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[r][e] = __builtin_fmaf(b, (float)a[e], acc[r][e]);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < MERGE_ROWS; ++r) {
+            T w[8];
+            __builtin_memcpy(w, &raw[r], 16);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) w[e] = (T)__builtin_fmaf(p.scale, acc[r][e], (float)w[e]);
+            __builtin_memcpy(&raw[r], w, 16);
+        }
     }
-    T* w = W + (int64_t)n * d + c;
-    const u32x4 wraw = *(const u32x4*)w;
-    T wv[8];
-    __builtin_memcpy(wv, &wraw, 16);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) wv[e] = (T)((float)wv[e] + scale * acc[e]);
-    u32x4 out;
-    __builtin_memcpy(&out, wv, 16);
-    *(u32x4*)w = out;
+    for (int r = 0; r < MERGE_ROWS; ++r) *(u32x4*)(dst + (int64_t)r * d) = raw[r];
 }
 }  // namespace
 
@@ -488,17 +510,25 @@ hipError_t launch_lora_pack(int dtype, const void* staging, size_t staging_layer
     return hipGetLastError();
 }
 
-hipError_t launch_lora_merge(int dtype, void* W, const void* Acat, const void* Bcat, int d, int kw, int rs,
-                             int slot, float scale, hipStream_t s) {
-    const int64_t threads = (int64_t)d * (d / 8);
-    const dim3 grid((unsigned)((threads + 255) / 256));
-    if (dtype == 1)
-        PB_LAUNCH(lora_merge_kernel<_Float16>, grid, dim3(256), 0, s, (_Float16*)W, (const _Float16*)Acat,
-                           (const _Float16*)Bcat, d, kw, rs, slot, scale);
-    else
-        PB_LAUNCH(lora_merge_kernel<__bf16>, grid, dim3(256), 0, s, (__bf16*)W, (const __bf16*)Acat,
-                           (const __bf16*)Bcat, d, kw, rs, slot, scale);
-    return hipGetLastError();
+hipError_t launch_lora_merge(int dtype, const MergeParams& all, hipStream_t s) {
+    if (all.d % 8 || all.d % MERGE_ROWS) return hipErrorInvalidValue;
+    constexpr int MAX_LAYERS = 16383;  // grid z limit / 4
+    for (int l0 = 0; l0 < all.layers; l0 += MAX_LAYERS) {
+        MergeParams p = all;
+        p.layers = std::min(MAX_LAYERS, all.layers - l0);
+        p.src += (int64_t)l0 * p.src_stride;
+        p.dst += (int64_t)l0 * p.dst_stride;
+        p.A = (const char*)p.A + (int64_t)l0 * 4 * p.kw * p.d * 2;
+        p.B = (const char*)p.B + (int64_t)l0 * 4 * p.kw * p.d * 2;
+        const dim3 grid((unsigned)((p.d / 8 + 255) / 256), (unsigned)(p.d / MERGE_ROWS), (unsigned)p.layers * 4);
+        if (dtype == 1)
+            PB_LAUNCH(lora_merge_kernel<_Float16>, grid, dim3(256), 0, s, p);
+        else
+            PB_LAUNCH(lora_merge_kernel<__bf16>, grid, dim3(256), 0, s, p);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace pb

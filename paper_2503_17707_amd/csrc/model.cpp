@@ -296,6 +296,7 @@ struct pb_model {
     bool ring_busy[STAGE_SLOTS] = {};
     int ring_next = 0;
     int merged_slot = -1;  // adapter merged into the device base weights (-1: none)
+    uint32_t merged_mask = 0;  // its targets (the slot may be attached anew meanwhile)
     bool shadow_valid = false;  // the shadow holds this load's unmerged attention weights
     // decode state: sequences of the last prefill, their length so far
     int dec_B = 0, dec_len = 0, dec_steps = 0;
@@ -1347,28 +1348,32 @@ extern "C" int pb_merge_lora(pb_model* m, int32_t slot) {
         if (int rc = wait_recorded(m, l)) return rc;
         HIP_TRY(hipStreamWaitEvent(s, m->ev_layer[l], 0));
     }
-    if (c.merge_shadow) {
-        if (m->merged_slot >= 0) {  // switch: back to the unmerged weights first
-            if (int rc = copy_shadow(m, false)) return rc;
-        } else if (!m->shadow_valid) {
-            if (int rc = copy_shadow(m, true)) return rc;
-            m->shadow_valid = true;
-        }
+    // a switch reads the unmerged weights from the shadow: targets that only
+    // the previous adapter changed go back unchanged in the same launch
+    const bool from_shadow = c.merge_shadow && m->merged_slot >= 0;
+    if (c.merge_shadow && !from_shadow && !m->shadow_valid) {
+        if (int rc = copy_shadow(m, true)) return rc;
+        m->shadow_valid = true;
     }
+    const uint32_t mask = m->slot_mask[slot];
+    pb::MergeParams p{};
+    char* layers = m->at(a.layers) + a.attn_w;  // Wq|Wk|Wv|Wo, consecutive [d, d] matrices (d a multiple of 128)
+    p.dst = layers;
+    p.dst_stride = (int64_t)a.layer_bytes;
+    p.src = from_shadow ? m->at(a.shadow) : layers;
+    p.src_stride = (int64_t)(from_shadow ? a.shadow_layer : a.layer_bytes);
+    p.A = m->at(a.loraA);
+    p.B = m->at(a.loraB);
+    p.layers = c.n_layers; p.d = c.d_model; p.kw = a.kw; p.rs = a.rs; p.slot = slot;
+    p.scale = m->slot_scale[slot];
+    p.merge_mask = mask;
+    p.copy_mask = from_shadow ? m->merged_mask & ~mask : 0u;
     m->merged_slot = -1;
     m->dec_B = 0;  // a KV cache from before the merge belongs to another model
-    const int tensor_of[4] = {PB_T_WQ, PB_T_WK, PB_T_WV, PB_T_WO};
-    for (int l = 0; l < c.n_layers; ++l) {
-        for (int t = 0; t < 4; ++t) {
-            if (!((m->slot_mask[slot] >> t) & 1u)) continue;
-            const char* At = m->at(a.loraA) + (size_t)l * a.loraA_layer + (size_t)t * a.kw * c.d_model * 2;
-            const char* Bt = m->at(a.loraB) + (size_t)l * a.loraB_layer + (size_t)t * c.d_model * a.kw * 2;
-            HIP_TRY(pb::launch_lora_merge(c.dtype, m->ltensor(l, tensor_of[t]), At, Bt, c.d_model, a.kw, a.rs, slot,
-                                          m->slot_scale[slot], s));
-        }
-    }
+    HIP_TRY(pb::launch_lora_merge(c.dtype, p, s));
     HIP_TRY(hipStreamSynchronize(s));
     m->merged_slot = slot;
+    m->merged_mask = mask;
     return PB_OK;
 }
 
