@@ -2,7 +2,7 @@
 // prompt tokens through self-attention; a prefill is causal, token j sees
 // tokens 0..j), flash-style: the T x T score matrix is never stored.
 //
-// Block = 4 waves of one (sequence, head); each wave owns 16 or 32 queries.
+// Block = 2 to 8 waves of one (sequence, head); each wave owns 16 or 32 queries.
 // Key/value tiles of 64 rows arrive row-major in a two-stage LDS ring by
 // LDS-DMA (the next tile loads while this one is used) and are consumed with
 // v_mfma_f32_16x16x32_{f16,bf16}:
@@ -439,13 +439,25 @@ template <typename T, int HD>
 hipError_t launch_qw(const void* qkv, const void* kv, int64_t kv_ld, int64_t kv_seq, void* out, int B,
                      int T_len, int H, hipStream_t s) {
     const long pairs = (long)H * B;
-    // 32 queries per wave when 128-query blocks still give every CU work;
-    // with fewer than 512 blocks of 64 queries, two wave groups split the keys
     const long blocks128 = (long)((T_len + 127) / 128) * pairs;
     const long blocks64 = (long)((T_len + 63) / 64) * pairs;
-    if (PB_ATTN_QW32 && blocks128 >= 512) return launch_hd<T, HD, 32, 1, 4, 2>(qkv, kv, kv_ld, kv_seq, out, B, T_len, H, s);
-    if (PB_ATTN_KS2 && blocks64 < 512 && T_len > BKV)
+    // Short prompts: a block no wider than the prompt (every wave beyond it
+    // only copies; H 32, hd 64: 200 x 20 tokens 24.2 us against 36.9 with 128
+    // queries per block, 64 x 64 tokens 18.0 against 20.0).
+    if constexpr (HD == 64)
+        if (T_len <= 32) return launch_hd<T, HD, 16, 1, 2, 2>(qkv, kv, kv_ld, kv_seq, out, B, T_len, H, s);
+    // Up to 512 blocks of 64 queries: two wave groups split the keys (1 x 1000
+    // tokens, H 32: 13.7 us against 17.0 at hd 64, 22.7 against 25.3 at 128)
+    if (PB_ATTN_KS2 && blocks64 <= 512 && T_len > BKV)
         return launch_hd<T, HD, 16, 2, 4, 2>(qkv, kv, kv_ld, kv_seq, out, B, T_len, H, s);
+    // 128 queries per block when that still gives every CU two: as 4 waves of
+    // 32 for head_dim 128 (fewer LDS reads per product), 8 waves of 16 for 64
+    // (more waves in flight: 48 x 77 tokens 19.3 us against 20.6, 1 x 2000
+    // 35.2 against 39.9, 16 x 250 equal)
+    if (T_len > 64 && blocks128 >= 512) {
+        if constexpr (HD == 64) return launch_hd<T, HD, 16, 1, 8, 2>(qkv, kv, kv_ld, kv_seq, out, B, T_len, H, s);
+        else if (PB_ATTN_QW32) return launch_hd<T, HD, 32, 1, 4, 2>(qkv, kv, kv_ld, kv_seq, out, B, T_len, H, s);
+    }
     return launch_hd<T, HD, 16, 1, 4, 2>(qkv, kv, kv_ld, kv_seq, out, B, T_len, H, s);
 }
 
