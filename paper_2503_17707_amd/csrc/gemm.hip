@@ -6,11 +6,12 @@
 // four consecutive output features of one token: the epilogue writes 8-byte
 // (dt) or 16-byte (fp32 residual) vectors.
 //
-// Block tile BM x BN, K tile 64: 256 x 256 (2-stage ring, 128 KiB of LDS) or
-// 128 x 128 (3-stage ring: with few tiles the weights arrive cold from HBM
-// and a deeper ring hides more of that latency) with 8 waves (2 x 4, two waves
-// per SIMD), chosen by how many tiles the shape gives, and 64 x 64 with 4
-// waves for N not a multiple of 128.  Tiles go straight from global memory
+// Block tile BM x BN, K tile 64: 256 x 256 (two wave groups in ping-pong over
+// a 2-stage ring, 128 KiB of LDS: gemm_pingpong_kernel) or 128 x 128 (3-stage
+// ring: with few tiles the weights arrive cold from HBM and a deeper ring
+// hides more of that latency) with 8 waves (2 x 4, two waves per SIMD), chosen
+// by how many tiles the shape gives, and 64 x 64 with 4 waves for N not a
+// multiple of 128.  Tiles go straight from global memory
 // into the S-stage LDS ring (LDS-DMA, no staging registers), so S-1 tiles are
 // in flight while one is multiplied; one barrier per K tile.  The operand
 // reads from LDS, not the MFMA rate, bound the smaller tiles: a wave's
@@ -62,9 +63,6 @@ namespace {
 #endif
 #ifndef PB_GEMV_RPB
 #define PB_GEMV_RPB 4  // output features per GEMV block
-#endif
-#ifndef PB_GEMM_S256
-#define PB_GEMM_S256 2  // ... of the 256 x 256 tiles
 #endif
 
 constexpr int ROW_BYTES = BK * 2;
@@ -242,23 +240,6 @@ void gemm_kernel(GemmParams p, SplitArgs sa) {
     for (int q = 0; q < S - 1; ++q)
         if (q < nk) issue(t_begin + q, q);
     int t = 0;
-    // 256 x 256 tiles except fc2: two tiles per trip, so that the ring stage
-    // of every copy and operand read is a constant (fewer address adds;
-    // measured qkv, o and fc1 0.8-2.4% faster at OPT-6.7B and 66B, fc2 1.5%
-    // slower, 128 x 128 tiles no faster)
-    if constexpr (S == 2 && BM == 256 && ROLE != 3) {
-        auto step = [&](int tt, auto st_c) {
-            constexpr int ST = decltype(st_c)::value;  // tt % 2
-            wait_vmcnt<0>();
-            __syncthreads();
-            issue(t_begin + tt + 1, ST ^ 1);
-            compute(ST);
-        };
-        for (; t + 2 < nk; t += 2) {
-            step(t, std::integral_constant<int, 0>{});
-            step(t + 1, std::integral_constant<int, 1>{});
-        }
-    }
     for (; t + S - 1 < nk; ++t) {
         wait_vmcnt<(S - 2) * NL>();  // tiles t+1 .. t+S-2 may still fly
         __syncthreads();             // tile t visible to all waves; stage of tile t-1 free
@@ -272,6 +253,197 @@ void gemm_kernel(GemmParams p, SplitArgs sa) {
     }
 
     store_tile<T, EPI, MF, NF>(p, jb, m0 + wm * WM, n0 + wn * WN, lr, lg, acc);
+}
+
+// ---- 256 x 256 tiles: two wave groups in ping-pong -----------------------------
+// Eight waves (2 x 4), wave tile 128 tokens x 64 features, K tile 64, two LDS
+// stages.  A K tile is four phases, one per quadrant (64 tokens x 32 features)
+// of the wave tile, and a phase has two slots, each closed by a barrier: a
+// memory slot (operand reads of the quadrant into registers, two copies) and a
+// product slot (16 products at raised wave priority).  Waves 4-7 run one slot
+// behind waves 0-3, and waves w and w + 4 share a SIMD, so one of the two is
+// always in its product slot while the other reads LDS: the matrix unit is not
+// left idle by operand reads, copy waits or the barrier, which held one third
+// of the cycles of the plain ring (0.60 MFMA busy).
+//
+// A stage is four regions in order of need: Wa (32 of each wave's 64 features),
+// X0 (64 of its 128 tokens), Wb, X1.  Quadrants go (Wa, X0), (Wb, X0),
+// (Wb, X1), (Wa, X1); Wa of the next tile is read in the last phase, into the
+// registers of this tile's Wb, so even tiles start with feature half 0 and odd
+// ones with half 1 and each memory slot holds 4 or 8 reads.  A region is free
+// once both groups have read it, one slot later, and is then refilled with
+// tile t + 2: every copy has seven phases to land with two stages only, and
+// every wait is for all but the 12 youngest of a wave's copies.  Past the last
+// tile the copies re-read it (they land in regions nobody reads).
+//
+// Bound by the matrix units at the clock the power limit leaves; OPT-66B fc1
+// (M 4096, N 36864, K 9216, f16) 2235 -> 2000 us (1245 -> 1395 TFLOP/s, the
+// vendor library 1406), M 2000, N 20480, K 5120 416 -> 361 us.  The K order of
+// every output is that of the plain loop (bit-identical results).
+template <typename T, int EPI, int ROLE>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
+void gemm_pingpong_kernel(GemmParams p, SplitArgs sa) {
+    typedef typename Mfma<T>::vec8 vec8;
+    constexpr int BM = 256, BN = 256;
+    constexpr int STAGE = (BM + BN) * ROW_BYTES;
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave & 1, wn = wave >> 1;
+    const TileJob jb = tile_job<BM, BN>(p, sa, (int)blockIdx.x, (int)gridDim.x);
+    const int m0 = jb.m0, n0 = jb.n0, nk1 = jb.nk1, t_begin = jb.t_begin, nk = jb.nk;
+
+    // copies: region X h is token rows 128 g + 64 h .. + 63 (g = 0, 1), region
+    // W h feature rows 64 g + 32 h .. + 31 (g = 0 .. 3), 16 copies of 8 rows
+    // each; copy q of this wave is number wave + 8 q of its region.  Lane i
+    // writes row i / 8, physical chunk i % 8.
+    const int lrow = lane >> 3;
+    const int chk = swz(lrow, lane & 7) * 8;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
+    int xrow[4], wrow[4];  // first row of copy q of region h: [2 h + q]
+    uint32_t xoff[4], woff[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int h = i >> 1, c = wave + 8 * (i & 1);
+        xrow[i] = (c >> 3) * 128 + h * 64 + (c & 7) * 8;
+        wrow[i] = (c >> 2) * 64 + h * 32 + (c & 3) * 8;
+        xoff[i] = ((uint32_t)min(m0 + xrow[i] + lrow, p.M - 1) * (uint32_t)p.ldx + chk) * 2;
+        woff[i] = ((uint32_t)min(n0 + wrow[i] + lrow, p.N - 1) * (uint32_t)p.ldw + chk) * 2;
+    }
+    // the LoRA K tiles' offsets are taken where they are used (the empty asm
+    // keeps the compiler from holding them in registers through the base tiles)
+    auto copy_x = [&](int t, int stage, int h) {
+        const uint32_t sb = lds0 + stage * STAGE;
+        t += t_begin;
+        if (t < nk1) {
+            const char* b = (const char*)p.X + (int64_t)t * BK * 2;
+#pragma unroll
+            for (int i = 2 * h; i < 2 * h + 2; ++i) dma16s(b, xoff[i], sb + xrow[i] * ROW_BYTES);
+        } else {
+            const char* b = (const char*)jb.X2 + (int64_t)(t - nk1) * BK * 2;
+#pragma unroll
+            for (int i = 2 * h; i < 2 * h + 2; ++i) {
+                int r = m0 + xrow[i] + lrow;
+                asm volatile("" : "+v"(r));
+                dma16s(b, ((uint32_t)min(r, p.M - 1) * (uint32_t)p.ldx2 + chk) * 2, sb + xrow[i] * ROW_BYTES);
+            }
+        }
+    };
+    auto copy_w = [&](int t, int stage, int h) {
+        const uint32_t sb = lds0 + stage * STAGE + BM * ROW_BYTES;
+        t += t_begin;
+        if (t < nk1) {
+            const char* b = (const char*)p.W + (int64_t)t * BK * 2;
+#pragma unroll
+            for (int i = 2 * h; i < 2 * h + 2; ++i) dma16s(b, woff[i], sb + wrow[i] * ROW_BYTES);
+        } else {
+            const char* b = (const char*)p.W2 + (int64_t)(t - nk1) * BK * 2;
+#pragma unroll
+            for (int i = 2 * h; i < 2 * h + 2; ++i) {
+                int r = n0 + wrow[i] + lrow;
+                asm volatile("" : "+v"(r));
+                dma16s(b, ((uint32_t)min(r, p.N - 1) * (uint32_t)p.ldw2 + chk) * 2, sb + wrow[i] * ROW_BYTES);
+            }
+        }
+    };
+
+    f32x4 acc[4][8];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int lr = lane & 15, lg = lane >> 4;
+    vec8 w0[2][2], w1[2][2], x[4][2];  // [fragment][k half]
+    const uint32_t lk[2] = {(uint32_t)(lr * ROW_BYTES + (swz(lr, lg) << 4)),
+                            (uint32_t)(lr * ROW_BYTES + (swz(lr, 4 + lg) << 4))};
+    auto read_w = [&](vec8 (&w)[2][2], int stage, int h) {
+        const uint8_t* s = smem + stage * STAGE + (BM + wn * 64 + h * 32) * ROW_BYTES;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) w[i][kk] = as_vec8<T>(*(const u32x4*)(s + i * 16 * ROW_BYTES + lk[kk]));
+    };
+    auto read_x = [&](int stage, int h) {
+        const uint8_t* s = smem + stage * STAGE + (wm * 128 + h * 64) * ROW_BYTES;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) x[j][kk] = as_vec8<T>(*(const u32x4*)(s + j * 16 * ROW_BYTES + lk[kk]));
+    };
+    // nothing moves across the end of a slot
+    auto barrier = [] { asm volatile("s_barrier" ::: "memory"); };
+    auto end_memory = [&] {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto products = [&](const vec8 (&w)[2][2], int fi, int fj) {
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[fi + i][fj + j] = Mfma<T>::mma(w[i][kk], x[j][kk], acc[fi + i][fj + j]);
+        __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_sched_barrier(0);
+        barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    const int last = nk - 1;
+    auto fill = [&](int t, int stage) {  // a whole stage, in order of need
+        copy_w(t, stage, stage);
+        copy_x(t, stage, 0);
+        copy_w(t, stage, 1 - stage);
+        copy_x(t, stage, 1);
+    };
+    fill(0, 0);
+    fill(min(1, last), 1);
+    wait_vmcnt<12>();
+    barrier();
+    read_w(w0, 0, 0);
+    end_memory();               // both groups hold Wa of tile 0: its region may be refilled
+    if (wave >= 4) barrier();  // one slot behind from here on
+    auto tile = [&](int t, auto parity) {
+        constexpr int P = decltype(parity)::value;  // t % 2: the stage, and the feature half of Wa
+        auto& wa = P ? w1 : w0;
+        auto& wb = P ? w0 : w1;
+        const int tn = min(t + 2, last);
+        read_x(P, 0);
+        copy_w(tn, P, P);
+        wait_vmcnt<12>();  // Wb landed
+        end_memory();
+        products(wa, 2 * P, 0);
+        read_w(wb, P, 1 - P);
+        copy_x(tn, P, 0);
+        wait_vmcnt<12>();  // X1 landed
+        end_memory();
+        products(wb, 2 - 2 * P, 0);
+        read_x(P, 1);
+        copy_w(tn, P, 1 - P);
+        wait_vmcnt<12>();  // Wa of t + 1 landed
+        end_memory();
+        products(wb, 2 - 2 * P, 4);
+        read_w(wb, 1 - P, 1 - P);  // Wa of t + 1
+        copy_x(tn, P, 1);
+        wait_vmcnt<12>();  // X0 of t + 1 landed
+        end_memory();
+        products(wa, 2 * P, 4);
+    };
+    const std::integral_constant<int, 0> even;
+    const std::integral_constant<int, 1> odd;
+    int t = 0;
+    for (; t + 1 < nk; t += 2) {
+        tile(t, even);
+        tile(t + 1, odd);
+    }
+    if (t < nk) tile(t, even);
+    if (wave < 4) barrier();  // as many barriers in both groups
+
+    store_tile<T, EPI, 8, 4>(p, jb, m0 + wm * 128, n0 + wn * 64, lr, lg, acc);
+    wait_vmcnt<0>();  // the last copies have landed before the block's LDS is given back
 }
 
 // ---- few rows (batched decode, short prompts): wide-row weight streaming ------
@@ -587,16 +759,20 @@ hipError_t finish_split(const GemmParams& p, const SplitArgs& sa, hipStream_t s)
 template <typename T, int EPI, int BM, int BN, int WGM, int WGN, int ROLE, int S>
 hipError_t launch_cfg(const GemmParams& p, const GemmWorkspace& wsp, int splits, int ragged_tail, hipStream_t s) {
     constexpr int LDS = S * (BM + BN) * ROW_BYTES;
+    constexpr auto kernel = [] {
+        if constexpr (BM == 256 && BN == 256) return &gemm_pingpong_kernel<T, EPI, ROLE>;
+        else return &gemm_kernel<T, EPI, BM, BN, WGM, WGN, ROLE, S>;
+    }();
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)gemm_kernel<T, EPI, BM, BN, WGM, WGN, ROLE, S>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        hipError_t e =
+            hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
     const TileGeometry g = tile_geometry<BM, BN>(p, wsp, splits, ragged_tail);
     const SplitArgs& sa = g.sa;
-    PB_LAUNCH((gemm_kernel<T, EPI, BM, BN, WGM, WGN, ROLE, S>), dim3(g.grid), dim3(64 * WGM * WGN), LDS, s, p, sa);
+    PB_LAUNCH(kernel, dim3(g.grid), dim3(64 * WGM * WGN), LDS, s, p, sa);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || sa.splits == 1) return e;
     if (sa.full_tiles > 0) {  // whole tiles, then the tail split
@@ -647,7 +823,7 @@ hipError_t launch_tiles(const GemmParams& p, const GemmWorkspace& wsp, hipStream
         return launch_cfg<T, EPI, 64, 64, 2, 2, 4, 4>(p, wsp, tp.splits, 0, s);
     } else {
         if (tp.tile == 256)
-            return launch_cfg<T, EPI, 256, 256, 2, 4, ROLE, PB_GEMM_S256>(p, wsp, tp.splits, tp.ragged_tail, s);
+            return launch_cfg<T, EPI, 256, 256, 2, 4, ROLE, 2>(p, wsp, tp.splits, tp.ragged_tail, s);
         if (tp.tile == 128)
             return launch_cfg<T, EPI, 128, 128, 2, 4, ROLE, PB_GEMM_S128>(p, wsp, tp.splits, tp.ragged_tail, s);
         return launch_cfg<T, EPI, 64, 64, 2, 2, ROLE, PB_GEMM_S64>(p, wsp, tp.splits, tp.ragged_tail, s);
