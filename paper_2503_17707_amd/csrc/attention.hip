@@ -446,9 +446,8 @@ hipError_t launch_qw(const void* qkv, const void* kv, int64_t kv_ld, int64_t kv_
     // queries per block, 64 x 64 tokens 18.0 against 20.0).
     if constexpr (HD == 64)
         if (T_len <= 32) return launch_hd<T, HD, 16, 1, 2, 2>(qkv, kv, kv_ld, kv_seq, out, B, T_len, H, s);
-    // Up to 512 blocks of 64 queries: two wave groups split the keys (1 x 1000
-    // tokens, H 32: 13.7 us against 17.0 at hd 64, 22.7 against 25.3 at 128)
-    if (PB_ATTN_KS2 && blocks64 <= 512 && T_len > BKV)
+    // with fewer than 512 blocks of 64 queries, two wave groups split the keys
+    if (PB_ATTN_KS2 && blocks64 < 512 && T_len > BKV)
         return launch_hd<T, HD, 16, 2, 4, 2>(qkv, kv, kv_ld, kv_seq, out, B, T_len, H, s);
     // 128 queries per block when that still gives every CU two: as 4 waves of
     // 32 for head_dim 128 (fewer LDS reads per product), 8 waves of 16 for 64

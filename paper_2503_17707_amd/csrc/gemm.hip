@@ -255,36 +255,40 @@ void gemm_kernel(GemmParams p, SplitArgs sa) {
     store_tile<T, EPI, MF, NF>(p, jb, m0 + wm * WM, n0 + wn * WN, lr, lg, acc);
 }
 
-// ---- 256 x 256 tiles: two wave groups in ping-pong -----------------------------
-// Eight waves (2 x 4), wave tile 128 tokens x 64 features, K tile 64, two LDS
-// stages.  A K tile is four phases, one per quadrant (64 tokens x 32 features)
-// of the wave tile, and a phase has two slots, each closed by a barrier: a
-// memory slot (operand reads of the quadrant into registers, two copies) and a
-// product slot (16 products at raised wave priority).  Waves 4-7 run one slot
+// ---- 256-feature tiles: two wave groups in ping-pong ----------------------------
+// Tiles of 64 XF tokens (XF = 2, 3 or 4) x 256 features; eight waves (2 x 4),
+// wave tile 32 XF tokens x 64 features, K tile 64, two LDS stages.  A K tile is
+// four phases, one per quadrant (16 XF tokens x 32 features) of the wave tile, and a phase has two slots, each closed by a barrier: a
+// memory slot (operand reads of the quadrant into registers, one or two copies)
+// and a product slot (4 XF products at raised wave priority).  Waves 4-7 run one slot
 // behind waves 0-3, and waves w and w + 4 share a SIMD, so one of the two is
 // always in its product slot while the other reads LDS: the matrix unit is not
 // left idle by operand reads, copy waits or the barrier, which held one third
 // of the cycles of the plain ring (0.60 MFMA busy).
 //
 // A stage is four regions in order of need: Wa (32 of each wave's 64 features),
-// X0 (64 of its 128 tokens), Wb, X1.  Quadrants go (Wa, X0), (Wb, X0),
+// X0 (half of its tokens), Wb, X1.  Quadrants go (Wa, X0), (Wb, X0),
 // (Wb, X1), (Wa, X1); Wa of the next tile is read in the last phase, into the
 // registers of this tile's Wb, so even tiles start with feature half 0 and odd
-// ones with half 1 and each memory slot holds 4 or 8 reads.  A region is free
+// ones with half 1 and each memory slot holds 4 or 2 XF reads.  A region is free
 // once both groups have read it, one slot later, and is then refilled with
 // tile t + 2: every copy has seven phases to land with two stages only, and
-// every wait is for all but the 12 youngest of a wave's copies.  Past the last
+// every wait is for all but the youngest one and a half tiles of a wave's copies.  Past the last
 // tile the copies re-read it (they land in regions nobody reads).
 //
 // Bound by the matrix units at the clock the power limit leaves; OPT-66B fc1
 // (M 4096, N 36864, K 9216, f16) 2235 -> 2000 us (1245 -> 1395 TFLOP/s, the
 // vendor library 1406), M 2000, N 20480, K 5120 416 -> 361 us.  The K order of
 // every output is that of the plain loop (bit-identical results).
-template <typename T, int EPI, int ROLE>
+template <typename T, int EPI, int XF, int ROLE>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
 void gemm_pingpong_kernel(GemmParams p, SplitArgs sa) {
     typedef typename Mfma<T>::vec8 vec8;
-    constexpr int BM = 256, BN = 256;
+    constexpr int BM = 64 * XF, BN = 256;
+    constexpr int XH = 16 * XF;            // tokens of a wave's X half
+    constexpr int XC = BM / 2 / 8;         // copies of an X region
+    constexpr int XQ = (XC + 7) / 8;       // ... per wave (XF = 3: four waves repeat the last one)
+    constexpr int LAG = (4 + 2 * XQ) * 3 / 2;  // copies younger than the one a slot needs
     constexpr int STAGE = (BM + BN) * ROW_BYTES;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const int lane = threadIdx.x & 63;
@@ -293,21 +297,25 @@ void gemm_pingpong_kernel(GemmParams p, SplitArgs sa) {
     const TileJob jb = tile_job<BM, BN>(p, sa, (int)blockIdx.x, (int)gridDim.x);
     const int m0 = jb.m0, n0 = jb.n0, nk1 = jb.nk1, t_begin = jb.t_begin, nk = jb.nk;
 
-    // copies: region X h is token rows 128 g + 64 h .. + 63 (g = 0, 1), region
-    // W h feature rows 64 g + 32 h .. + 31 (g = 0 .. 3), 16 copies of 8 rows
-    // each; copy q of this wave is number wave + 8 q of its region.  Lane i
-    // writes row i / 8, physical chunk i % 8.
+    // copies: region X h is token rows (2 g + h) XH .. + XH - 1 (g = 0, 1),
+    // region W h feature rows 64 g + 32 h .. + 31 (g = 0 .. 3), 8 rows per copy;
+    // copy q of this wave is number wave + 8 q of its region.  Lane i writes
+    // row i / 8, physical chunk i % 8.
     const int lrow = lane >> 3;
     const int chk = swz(lrow, lane & 7) * 8;
     const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
-    int xrow[4], wrow[4];  // first row of copy q of region h: [2 h + q]
-    uint32_t xoff[4], woff[4];
+    int xrow[2 * XQ], wrow[4];  // first row of copy q of region h: [XQ h + q], [2 h + q]
+    uint32_t xoff[2 * XQ], woff[4];
+#pragma unroll
+    for (int i = 0; i < 2 * XQ; ++i) {
+        const int h = i / XQ, c = min(wave + 8 * (i % XQ), XC - 1);
+        xrow[i] = (2 * (c / (XC / 2)) + h) * XH + (c % (XC / 2)) * 8;
+        xoff[i] = ((uint32_t)min(m0 + xrow[i] + lrow, p.M - 1) * (uint32_t)p.ldx + chk) * 2;
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int h = i >> 1, c = wave + 8 * (i & 1);
-        xrow[i] = (c >> 3) * 128 + h * 64 + (c & 7) * 8;
         wrow[i] = (c >> 2) * 64 + h * 32 + (c & 3) * 8;
-        xoff[i] = ((uint32_t)min(m0 + xrow[i] + lrow, p.M - 1) * (uint32_t)p.ldx + chk) * 2;
         woff[i] = ((uint32_t)min(n0 + wrow[i] + lrow, p.N - 1) * (uint32_t)p.ldw + chk) * 2;
     }
     // the LoRA K tiles' offsets are taken where they are used (the empty asm
@@ -318,11 +326,11 @@ void gemm_pingpong_kernel(GemmParams p, SplitArgs sa) {
         if (t < nk1) {
             const char* b = (const char*)p.X + (int64_t)t * BK * 2;
 #pragma unroll
-            for (int i = 2 * h; i < 2 * h + 2; ++i) dma16s(b, xoff[i], sb + xrow[i] * ROW_BYTES);
+            for (int i = XQ * h; i < XQ * h + XQ; ++i) dma16s(b, xoff[i], sb + xrow[i] * ROW_BYTES);
         } else {
             const char* b = (const char*)jb.X2 + (int64_t)(t - nk1) * BK * 2;
 #pragma unroll
-            for (int i = 2 * h; i < 2 * h + 2; ++i) {
+            for (int i = XQ * h; i < XQ * h + XQ; ++i) {
                 int r = m0 + xrow[i] + lrow;
                 asm volatile("" : "+v"(r));
                 dma16s(b, ((uint32_t)min(r, p.M - 1) * (uint32_t)p.ldx2 + chk) * 2, sb + xrow[i] * ROW_BYTES);
@@ -347,13 +355,13 @@ void gemm_pingpong_kernel(GemmParams p, SplitArgs sa) {
         }
     };
 
-    f32x4 acc[4][8];
+    f32x4 acc[4][2 * XF];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < 2 * XF; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int lr = lane & 15, lg = lane >> 4;
-    vec8 w0[2][2], w1[2][2], x[4][2];  // [fragment][k half]
+    vec8 w0[2][2], w1[2][2], x[XF][2];  // [fragment][k half]
     const uint32_t lk[2] = {(uint32_t)(lr * ROW_BYTES + (swz(lr, lg) << 4)),
                             (uint32_t)(lr * ROW_BYTES + (swz(lr, 4 + lg) << 4))};
     auto read_w = [&](vec8 (&w)[2][2], int stage, int h) {
@@ -364,9 +372,9 @@ void gemm_pingpong_kernel(GemmParams p, SplitArgs sa) {
             for (int kk = 0; kk < 2; ++kk) w[i][kk] = as_vec8<T>(*(const u32x4*)(s + i * 16 * ROW_BYTES + lk[kk]));
     };
     auto read_x = [&](int stage, int h) {
-        const uint8_t* s = smem + stage * STAGE + (wm * 128 + h * 64) * ROW_BYTES;
+        const uint8_t* s = smem + stage * STAGE + (2 * wm + h) * XH * ROW_BYTES;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < XF; ++j)
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk) x[j][kk] = as_vec8<T>(*(const u32x4*)(s + j * 16 * ROW_BYTES + lk[kk]));
     };
@@ -384,7 +392,7 @@ void gemm_pingpong_kernel(GemmParams p, SplitArgs sa) {
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
+                for (int j = 0; j < XF; ++j)
                     acc[fi + i][fj + j] = Mfma<T>::mma(w[i][kk], x[j][kk], acc[fi + i][fj + j]);
         __builtin_amdgcn_s_setprio(0);
         __builtin_amdgcn_sched_barrier(0);
@@ -401,7 +409,7 @@ void gemm_pingpong_kernel(GemmParams p, SplitArgs sa) {
     };
     fill(0, 0);
     fill(min(1, last), 1);
-    wait_vmcnt<12>();
+    wait_vmcnt<LAG>();
     barrier();
     read_w(w0, 0, 0);
     end_memory();               // both groups hold Wa of tile 0: its region may be refilled
@@ -413,24 +421,24 @@ void gemm_pingpong_kernel(GemmParams p, SplitArgs sa) {
         const int tn = min(t + 2, last);
         read_x(P, 0);
         copy_w(tn, P, P);
-        wait_vmcnt<12>();  // Wb landed
+        wait_vmcnt<LAG>();  // Wb landed
         end_memory();
         products(wa, 2 * P, 0);
         read_w(wb, P, 1 - P);
         copy_x(tn, P, 0);
-        wait_vmcnt<12>();  // X1 landed
+        wait_vmcnt<LAG>();  // X1 landed
         end_memory();
         products(wb, 2 - 2 * P, 0);
         read_x(P, 1);
         copy_w(tn, P, 1 - P);
-        wait_vmcnt<12>();  // Wa of t + 1 landed
+        wait_vmcnt<LAG>();  // Wa of t + 1 landed
         end_memory();
-        products(wb, 2 - 2 * P, 4);
+        products(wb, 2 - 2 * P, XF);
         read_w(wb, 1 - P, 1 - P);  // Wa of t + 1
         copy_x(tn, P, 1);
-        wait_vmcnt<12>();  // X0 of t + 1 landed
+        wait_vmcnt<LAG>();  // X0 of t + 1 landed
         end_memory();
-        products(wa, 2 * P, 4);
+        products(wa, 2 * P, XF);
     };
     const std::integral_constant<int, 0> even;
     const std::integral_constant<int, 1> odd;
@@ -442,24 +450,26 @@ void gemm_pingpong_kernel(GemmParams p, SplitArgs sa) {
     if (t < nk) tile(t, even);
     if (wave < 4) barrier();  // as many barriers in both groups
 
-    store_tile<T, EPI, 8, 4>(p, jb, m0 + wm * 128, n0 + wn * 64, lr, lg, acc);
+    store_tile<T, EPI, 2 * XF, 4>(p, jb, m0 + wm * 2 * XH, n0 + wn * 64, lr, lg, acc);
     wait_vmcnt<0>();  // the last copies have landed before the block's LDS is given back
 }
 
 // ---- few rows (batched decode, short prompts): wide-row weight streaming ------
-// One block computes all (at most BM) tokens x BN output features over one K
-// range; its waves split the features (and the tokens when WGM > 1).  A ring
+// One block computes BM tokens (all of them up to 32 or 64) x BN output features
+// over one K range; its waves split the features (and the tokens when WGM > 1).  A ring
 // stage holds BKE (128 or 256) K elements of the BM token rows and BN weight
 // rows, so a copy instruction fetches whole 256- or 512-byte row pieces; the
 // 128-byte pieces of the tiles above reach 3.5 TB/s on such products, these
 // 4.9 (N 16384, K 4096, 32 rows: 27.4 us against 37.3; N 2048, K 8192: 8.7
 // and a reduce against 16.6).  HBM-bound for large N, by its fixed ~3 us for
-// small ones.  The base K range of every wave is independent of the LoRA
-// segment (B = 0 stays bit-identical to the base), whose few columns are read
+// small ones.  An unsplit launch still adds the K ranges of plan_tiles' split
+// one after another (the same result as its partials and reduce, bit for bit).
+// The base K ranges are independent of the LoRA segment (B = 0 stays
+// bit-identical to the base), whose few columns are read
 // straight into registers: the first 64, requested ahead of the ring, have
 // landed by the time the base is done.
 template <typename T, int EPI, int BM, int BN, int WGM, int WGN, int BKE, int S, int ROLE>
-__global__ __launch_bounds__(64 * WGM * WGN) void stream_kernel(GemmParams p, SplitArgs sa) {
+__global__ __launch_bounds__(64 * WGM * WGN) void stream_kernel(GemmParams p, SplitArgs sa, int kst) {
     typedef typename Mfma<T>::vec8 vec8;
     constexpr int NW = WGM * WGN;
     constexpr int WM = BM / WGM, WN = BN / WGN;
@@ -477,10 +487,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void stream_kernel(GemmParams p, Sp
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave % WGM, wn = wave / WGM;
     const int lr = lane & 15, lg = lane >> 4;
-    const int nbn = p.N / BN;
-    const int split = (int)blockIdx.x / nbn, n0 = ((int)blockIdx.x % nbn) * BN;
-    const int nk = p.K1 / BKE;
-    const int t0 = stream_stage(nk, split, sa.splits), n = stream_stage(nk, split + 1, sa.splits) - t0;
+    const StreamJob job = stream_job<BM, BN, BKE>(p, kst, (int)blockIdx.x, (int)gridDim.x);
+    const int split = job.split, m0 = job.m0, n0 = job.n0, t0 = job.t0, n = job.n;
 
     // copy j of this wave fills rows RPI (wave + NW j) .. of a stage, tokens
     // first; the 16-byte chunks of a row are XOR-permuted by its low row bits
@@ -491,7 +499,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void stream_kernel(GemmParams p, Sp
         const int row = (wave + NW * j) * RPI + lane / CPR;
         const int ch = (lane % CPR) ^ (row & 15);
         off[j] = (wave + NW * j) * RPI < BM
-                     ? ((uint32_t)min(row, p.M - 1) * (uint32_t)p.ldx + ch * 8) * 2
+                     ? ((uint32_t)min(m0 + row, p.M - 1) * (uint32_t)p.ldx + ch * 8) * 2
                      : ((uint32_t)(n0 + row - BM) * (uint32_t)p.ldw + ch * 8) * 2;
     }
     const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
@@ -506,15 +514,35 @@ __global__ __launch_bounds__(64 * WGM * WGN) void stream_kernel(GemmParams p, Sp
         }
     };
 
-    f32x4 acc[NF][MF];
+    // acc: the K range at hand; sum: the ranges closed so far (-0 + x is x)
+    f32x4 acc[NF][MF], sum[NF][MF];
 #pragma unroll
     for (int i = 0; i < NF; ++i)
 #pragma unroll
-        for (int j = 0; j < MF; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < MF; ++j) {
+            acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            sum[i][j] = f32x4{-0.f, -0.f, -0.f, -0.f};
+        }
+    auto close_range = [&] {
+#pragma unroll
+        for (int i = 0; i < NF; ++i)
+#pragma unroll
+            for (int j = 0; j < MF; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    sum[i][j][r] += acc[i][j][r];
+                    acc[i][j][r] = 0.f;
+                }
+    };
+    int left = sa.kt_split;  // K tiles of 64 until the range at hand ends
     auto compute = [&](int stage) {
         const uint8_t* s = smem + stage * STAGE;
 #pragma unroll
         for (int kk = 0; kk < BKE / 32; ++kk) {
+            if (kk % 2 == 0 && left-- == 0) {  // the tile after a range's last
+                close_range();
+                left = sa.kt_split - 1;
+            }
             const int ch = kk * 4 + lg;
             vec8 b[MF];
 #pragma unroll
@@ -552,7 +580,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void stream_kernel(GemmParams p, Sp
             o.w[i] = *(const u32x4*)((const T*)p.W2 + (int64_t)(n0 + wn * WN + i * 16 + lr) * p.ldw2 + t * 32 + 8 * lg);
 #pragma unroll
         for (int j = 0; j < MF; ++j)
-            o.x[j] = *(const u32x4*)(X2 + (int64_t)min(wm * WM + j * 16 + lr, p.M - 1) * p.ldx2 + t * 32 + 8 * lg);
+            o.x[j] = *(const u32x4*)(X2 + (int64_t)min(m0 + wm * WM + j * 16 + lr, p.M - 1) * p.ldx2 + t * 32 + 8 * lg);
     };
     auto mul2 = [&](const Ops& o) {
 #pragma unroll
@@ -593,12 +621,13 @@ __global__ __launch_bounds__(64 * WGM * WGN) void stream_kernel(GemmParams p, Sp
             mul2(l1);
         }
     }
+    close_range();
     TileJob jb;
     jb.partial = sa.splits > 1;
     jb.pbase = sa.ws + (int64_t)split * p.M * p.N;
     jb.ldp = p.N;
     jb.om = jb.on = 0;
-    store_tile<T, EPI, MF, NF>(p, jb, wm * WM, n0 + wn * WN, lr, lg, acc);
+    store_tile<T, EPI, MF, NF>(p, jb, m0 + wm * WM, n0 + wn * WN, lr, lg, sum);
 }
 
 // Sum the split-K partials in split order, then apply the epilogue.
@@ -718,25 +747,22 @@ hipError_t launch_resid_ln(const GemmParams& p, const SplitArgs& sa, hipStream_t
     PB_LAUNCH((splitk_resid_ln_kernel<T, ROLE, MAXC, NS>), dim3(p.M), dim3(256), 0, s, p, sa)
     // few rows (latency-bound): every partial in flight at once; many rows:
     // occupancy hides the latency and registers matter more
-    if (p.N <= 2048) {
-        if (sa.splits == 2) PB_RLN(2, 2);
-        else if (sa.splits == 3) PB_RLN(2, 3);
-        else if (sa.splits == 4) PB_RLN(2, 4);
-        else if (sa.splits == 6) PB_RLN(2, 6);
-        else if (sa.splits == 8) PB_RLN(2, 8);
-        else PB_RLN(2, 0);
-    } else if (p.N <= 4096) {
-        if (sa.splits == 2) PB_RLN(4, 2);
-        else if (sa.splits == 3) PB_RLN(4, 3);
-        else if (sa.splits == 4) PB_RLN(4, 4);
-        else if (sa.splits == 6) PB_RLN(4, 6);
-        else if (sa.splits == 8) PB_RLN(4, 8);
-        else PB_RLN(4, 0);
-    } else if (p.N <= 8192) {
-        PB_RLN(8, 0);
-    } else {
-        PB_RLN(RLN_MAXC, 0);
-    }
+#define PB_RLN_NS(MAXC)                       \
+    do {                                      \
+        if (sa.splits == 2) PB_RLN(MAXC, 2);      \
+        else if (sa.splits == 3) PB_RLN(MAXC, 3); \
+        else if (sa.splits == 4) PB_RLN(MAXC, 4); \
+        else if (sa.splits == 5) PB_RLN(MAXC, 5); \
+        else if (sa.splits == 6) PB_RLN(MAXC, 6); \
+        else if (sa.splits == 7) PB_RLN(MAXC, 7); \
+        else if (sa.splits == 8) PB_RLN(MAXC, 8); \
+        else PB_RLN(MAXC, 0);                     \
+    } while (0)
+    if (p.N <= 2048) PB_RLN_NS(2);
+    else if (p.N <= 4096) PB_RLN_NS(4);
+    else if (p.N <= 8192) PB_RLN(8, 0);
+    else PB_RLN(RLN_MAXC, 0);
+#undef PB_RLN_NS
 #undef PB_RLN
     return hipGetLastError();
 }
@@ -760,7 +786,7 @@ template <typename T, int EPI, int BM, int BN, int WGM, int WGN, int ROLE, int S
 hipError_t launch_cfg(const GemmParams& p, const GemmWorkspace& wsp, int splits, int ragged_tail, hipStream_t s) {
     constexpr int LDS = S * (BM + BN) * ROW_BYTES;
     constexpr auto kernel = [] {
-        if constexpr (BM == 256 && BN == 256) return &gemm_pingpong_kernel<T, EPI, ROLE>;
+        if constexpr (BN == 256) return &gemm_pingpong_kernel<T, EPI, BM / 64, ROLE>;
         else return &gemm_kernel<T, EPI, BM, BN, WGM, WGN, ROLE, S>;
     }();
     static bool attr_set = false;
@@ -775,17 +801,19 @@ hipError_t launch_cfg(const GemmParams& p, const GemmWorkspace& wsp, int splits,
     PB_LAUNCH(kernel, dim3(g.grid), dim3(64 * WGM * WGN), LDS, s, p, sa);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || sa.splits == 1) return e;
-    if (sa.full_tiles > 0) {  // whole tiles, then the tail split
-        const int64_t groups = (int64_t)sa.tail_tiles * (BM * BN / 4);
-        PB_LAUNCH((tail_reduce_kernel<T, EPI, ROLE, BM, BN>), dim3((unsigned)((groups + 255) / 256)), dim3(256), 0,
-                  s, p, sa);
-        return hipGetLastError();
+    if constexpr (BM == BN) {
+        if (sa.full_tiles > 0) {  // whole tiles, then the tail split
+            const int64_t groups = (int64_t)sa.tail_tiles * (BM * BN / 4);
+            PB_LAUNCH((tail_reduce_kernel<T, EPI, ROLE, BM, BN>), dim3((unsigned)((groups + 255) / 256)), dim3(256),
+                      0, s, p, sa);
+            return hipGetLastError();
+        }
     }
     return finish_split<T, EPI, ROLE>(p, sa, s);
 }
 
 template <typename T, int EPI, int BM, int BN, int WGM, int WGN, int BKE, int S, int ROLE>
-hipError_t launch_stream_cfg(const GemmParams& p, const GemmWorkspace& wsp, int splits, hipStream_t s) {
+hipError_t launch_stream_cfg(const GemmParams& p, const GemmWorkspace& wsp, const WidePlan& w, hipStream_t s) {
     constexpr int LDS = S * (BM + BN) * BKE * 2;
     static bool attr_set = false;
     if (!attr_set) {
@@ -795,30 +823,41 @@ hipError_t launch_stream_cfg(const GemmParams& p, const GemmWorkspace& wsp, int 
         attr_set = true;
     }
     SplitArgs sa{};
-    sa.splits = splits;
+    sa.splits = w.splits;
+    sa.kt_split = w.kt;
     sa.ws = (float*)wsp.ws;
-    PB_LAUNCH((stream_kernel<T, EPI, BM, BN, WGM, WGN, BKE, S, ROLE>), dim3(p.N / BN * splits),
-              dim3(64 * WGM * WGN), LDS, s, p, sa);
+    const int kst = w.splits > 1 ? w.kt * BK / BKE : p.K1 / BKE;  // ring stages per launched range
+    PB_LAUNCH((stream_kernel<T, EPI, BM, BN, WGM, WGN, BKE, S, ROLE>), dim3((unsigned)((p.M + BM - 1) / BM * (p.N / BN) * w.splits)),
+              dim3(64 * WGM * WGN), LDS, s, p, sa, kst);
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || splits == 1) return e;
+    if (e != hipSuccess || w.splits == 1) return e;
     return finish_split<T, EPI, ROLE>(p, sa, s);
 }
 
 template <typename T, int EPI, int ROLE>
-hipError_t launch_stream(const GemmParams& p, const GemmWorkspace& wsp, const StreamPlan& sp, hipStream_t s) {
-    if (sp.bm == 64) return launch_stream_cfg<T, EPI, 64, 64, 1, 4, 128, 4, ROLE>(p, wsp, sp.splits, s);
-    if (sp.bn == 32) return launch_stream_cfg<T, EPI, 32, 32, 1, 2, 128, 4, ROLE>(p, wsp, sp.splits, s);
-    if (sp.bk == 256) return launch_stream_cfg<T, EPI, 32, 64, 1, 4, 256, 3, ROLE>(p, wsp, sp.splits, s);
-    return launch_stream_cfg<T, EPI, 32, 64, 1, 4, 128, 3, ROLE>(p, wsp, sp.splits, s);
+hipError_t launch_wide(const GemmParams& p, const GemmWorkspace& wsp, const WidePlan& w, hipStream_t s) {
+    if (w.kind == WIDE_RING) {
+        if (w.bm == 192) return launch_cfg<T, EPI, 192, 128, 2, 4, ROLE, 4>(p, wsp, w.splits, 0, s);
+        return launch_cfg<T, EPI, 128, 128, 2, 4, ROLE, PB_GEMM_S128>(p, wsp, w.splits, 0, s);
+    }
+    if (w.kind == WIDE_PINGPONG) {
+        if (w.bm == 192) return launch_cfg<T, EPI, 192, 256, 2, 4, ROLE, 2>(p, wsp, w.splits, 0, s);
+        return launch_cfg<T, EPI, 128, 256, 2, 4, ROLE, 2>(p, wsp, w.splits, 0, s);
+    }
+    if (w.bm == 128) return launch_stream_cfg<T, EPI, 128, 64, 4, 2, 128, 3, ROLE>(p, wsp, w, s);
+    if (w.bm == 64) return launch_stream_cfg<T, EPI, 64, 64, 1, 4, 128, 4, ROLE>(p, wsp, w, s);
+    if (w.bn == 32) return launch_stream_cfg<T, EPI, 32, 32, 1, 2, 128, 4, ROLE>(p, wsp, w, s);
+    if (w.bk == 256) return launch_stream_cfg<T, EPI, 32, 64, 1, 4, 256, 3, ROLE>(p, wsp, w, s);
+    return launch_stream_cfg<T, EPI, 32, 64, 1, 4, 128, 3, ROLE>(p, wsp, w, s);
 }
 
 template <typename T, int EPI, int ROLE>
 hipError_t launch_tiles(const GemmParams& p, const GemmWorkspace& wsp, hipStream_t s) {
-    if constexpr (ROLE != 4) {
-        const StreamPlan sp = plan_stream(p, wsp);
-        if (sp.bm) return launch_stream<T, EPI, ROLE>(p, wsp, sp, s);
-    }
     const TilePlan tp = plan_for_role(ROLE, p, wsp);
+    if constexpr (ROLE != 4) {
+        const WidePlan w = plan_wide(p, wsp, tp);
+        if (w.kind != WIDE_NONE) return launch_wide<T, EPI, ROLE>(p, wsp, w, s);
+    }
     if constexpr (ROLE == 4) {
         return launch_cfg<T, EPI, 64, 64, 2, 2, 4, 4>(p, wsp, tp.splits, 0, s);
     } else {
@@ -987,11 +1026,15 @@ hipError_t launch_gemm(int dtype, int role, int epi, const GemmParams& p, const 
     const int expect[5] = {EPI_QKV, EPI_RESID, EPI_RELU, EPI_RESID, EPI_SHRINK};
     if (role < 0 || role > 4 || expect[role] != epi) return hipErrorInvalidValue;
     // The GEMV's fp32 dot products cost arithmetic per row (N 8192, K 2048: 7.6
-    // us for 1 row, 13.2 for 4, 22.8 for 8), the wide-row streaming kernel's
-    // matrix products do not (8-10 us up to 32 rows): the GEMV takes 1 and 2
-    // rows, and up to 8 where that kernel does not apply (the LoRA shrink, K
-    // not a multiple of 128).
-    if (PB_GEMM_GEMV && (p.M <= 2 || (p.M <= GEMV_MAX_ROWS && (role == 4 || !plan_stream(p, wsp).bm))))
+    // us for 1 row, 13.1 for 4, 22.5 for 8), the streaming kernel's matrix
+    // products do not (10.2 us up to 16 rows): the GEMV takes 1 and 2 rows, 3
+    // and 4 for few features, where the streaming kernel would need a reduce
+    // launch (N 2048, K 2048: 6.1 us against 8.1; N 5120, K 20480: 40.4 against
+    // 42.3; not where the LayerNorm that follows is that reduce), and up to 8
+    // where that kernel does not apply (the LoRA shrink, K not a multiple of 128).
+    const bool gemv = p.M <= 2 || (p.M <= 4 && p.N <= 5120 && !p.ln_out) ||
+                      (p.M <= GEMV_MAX_ROWS && (role == 4 || p.K1 % 128));
+    if (PB_GEMM_GEMV && gemv)
         return dtype == 1 ? launch_gemv_typed<_Float16>(role, p, s) : launch_gemv_typed<__bf16>(role, p, s);
     if (dtype == 1) return launch_typed<_Float16>(role, p, wsp, s);
     return launch_typed<__bf16>(role, p, wsp, s);

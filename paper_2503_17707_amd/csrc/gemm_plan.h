@@ -231,54 +231,132 @@ TilePlan plan_tiles(const GemmParams& p, const GemmWorkspace& wsp) {
     return best;
 }
 
-// Few token rows (more than the GEMV takes, at most STREAM_MAX_ROWS): the
-// weights are streamed through a ring of wide LDS rows (128 or 256 K elements
-// per row), one block of all tokens x `bn` output features per K range.
-constexpr int STREAM_MAX_ROWS = 64;
+// Launches between the GEMV and the large tiles: the streaming kernel (wide
+// LDS rows, `bm` tokens x `bn` features per block) up to STREAM_MAX_ROWS rows,
+// and tile shapes beside the square ones of plan_tiles.
+constexpr int STREAM_MAX_ROWS = 512;
 
-struct StreamPlan {
-    int bm;      // tokens per block (32 or 64); 0: not a stream launch
-    int bn;      // output features per block (64 or 32)
-    int bk;      // K elements per ring stage (128 or 256)
-    int splits;  // K ranges
+enum WideKind { WIDE_NONE = 0, WIDE_STREAM, WIDE_RING, WIDE_PINGPONG };
+
+struct WidePlan {
+    int kind;    // WideKind; WIDE_NONE: plan_tiles' choice stands
+    int bm, bn;  // stream: 32 x 64, 32 x 32, 64 x 64, 128 x 64; ring: 128 or 192 x 128; ping-pong: 128 or 192 x 256
+    int bk;      // stream: K elements per ring stage (128 or 256)
+    int splits;  // K ranges launched
+    int kt;      // stream: K tiles (of 64) per range of plan_tiles' split (the sum's order), or all of them
 };
 
-// K ranges of a stream launch: `splits` nearly equal runs of K stages
-// (split s takes stages [nk s / splits, nk (s + 1) / splits)).
-__host__ __device__ __forceinline__ int stream_stage(int nk, int split, int splits) {
-    return (int)((int64_t)nk * split / splits);
+// Block bid of a stream launch -> its tile corner, K split and stages of that
+// split (split s takes stages [s kst, (s + 1) kst), the last one the rest).
+// Token tiles of one feature block are neighbours within an XCD's run (they
+// share its weight rows).
+struct StreamJob {
+    int m0, n0, split, t0, n;
+};
+
+template <int BM, int BN, int BKE>
+__host__ __device__ __forceinline__ StreamJob stream_job(const GemmParams& p, int kst, int bid, int nblk) {
+    const int nbm = (p.M + BM - 1) / BM, tiles = p.N / BN * nbm;
+    if (nbm > 1 && (nblk & 7) == 0) bid = (bid & 7) * (nblk >> 3) + (bid >> 3);
+    StreamJob j;
+    j.split = bid / tiles;
+    j.m0 = bid % tiles % nbm * BM;
+    j.n0 = bid % tiles / nbm * BN;
+    const int nk = p.K1 / BKE;
+    j.t0 = j.split * kst;
+    j.n = nk - j.t0 < kst ? nk - j.t0 : kst;
+    return j;
 }
 
-// Block shape and K split of a stream launch.  Measured on gfx950: one CU
-// copies ~45 GB/s into LDS whatever the block shape, the chip streams cold
-// weights at ~5.2 TB/s, a launch costs ~3 us beside that, a separate reduce
-// of split partials ~4 us; where a LayerNorm follows (ln_out) the reduce is
-// that LayerNorm's own pass and a split costs only its partials' reads.  The
-// model below is within 15% of the measured times over M = 16 .. 64, N = 2048
-// .. 16384, K = 2048 .. 16384.  K not a multiple of 128 is left to the tiles.
-StreamPlan plan_stream(const GemmParams& p, const GemmWorkspace& wsp) {
-    StreamPlan best{0, 0, 0, 1};
-    if (p.M > STREAM_MAX_ROWS || p.K1 % 128) return best;
-    const int bm = p.M <= 32 ? 32 : 64;
-    const double floor_t = (double)p.N * p.K1 * 2 / 5.2e12;
-    double best_t = 1e30;
-    for (int bn : {64, 32}) {
-        if (bm == 64 && bn == 32) continue;
-        for (int s : {1, 2, 3, 4, 6, 8}) {
-            if (s > 1 && (p.K1 / 128 / s < 4 || !wsp.ws || (double)p.M * p.N * 4 * s > (double)wsp.bytes)) break;
-            const long per_cu = ((long)(p.N / bn) * s + 255) / 256;  // blocks of the busiest CU
-            const double copy_t = per_cu * ((double)p.K1 / s) * (bm + bn) * 2 / 45e9;
-            double t = std::max(copy_t, floor_t);
-            if (s > 1) t += p.ln_out ? 0.3e-6 * s : 4e-6;
-            if (t < best_t * 0.98) {  // the simpler plan on near ties
-                best_t = t;
-                best = {bm, bn, 128, s};
-            }
+// What a K split or its absence costs beside the product: partials written and
+// read (mostly from the last-level cache: ~8 TB/s) and a reduce launch of its
+// own (4 us) unless the LayerNorm that follows is that reduce; without a split
+// that LayerNorm is a pass.
+inline double split_cost(const GemmParams& p, int splits) {
+    const double out = (double)p.M * p.N * 4;
+    if (splits > 1) return 2.0 * out * splits / 8e12 + (p.ln_out ? 0.0 : 4e-6);
+    return p.ln_out ? out * 1.5 / 4e12 + 3e-6 : 0.0;
+}
+
+// Time of a tile launch: rounds of 256 blocks (one per CU) at the measured
+// time per 64-wide K tile (M 100 .. 2000, cold weights), and the launch, the
+// ring's first tiles and the epilogue.
+inline double tile_time(const GemmParams& p, int bm, int bn, int splits) {
+    const long tiles = (long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn);
+    const long blocks = tiles * splits;
+    double per_kt;
+    if (bn == 256) per_kt = bm == 256 ? 1.7e-6 : bm == 192 ? 1.36e-6 : 1.06e-6;
+    else if (bm == 192) per_kt = 0.84e-6;
+    else if (bm == 128) per_kt = 0.47e-6 + 0.22e-6 * (double)std::min<long>(blocks, 256) / 256;
+    else per_kt = 0.30e-6;
+    const double fixed = bn == 256 ? 6e-6 : 4e-6;
+    double t = (double)((blocks + 255) / 256) * (double)((p.K1 / BK + splits - 1) / splits) * per_kt;
+    // eight K ranges a multiple of 4 KB apart read the same HBM channels (N
+    // 4096, K 16384, 100 rows: 51.8 us, six ranges 40.1)
+    if (splits == 8 && (p.K1 / 8 * 2) % 4096 == 0) t *= 1.5;
+    t = std::max(t, (double)p.N * p.K1 * 2 / 4.8e12);  // cold weights in 128-byte row pieces
+    return fixed + t + split_cost(p, splits);
+}
+
+// Time of a stream launch: a CU copies ~60 GB/s into LDS whatever the block
+// shape (blocks on one CU share it), the chip streams cold weights at ~5.2
+// TB/s, the two overlap but for a fifth of the shorter; ~3 us beside that, and
+// 2 more per further round of blocks that fill a CU's LDS (all but the 32-row
+// ones).  Within 15% of the measured times over M = 16 .. 333, N = 2048 ..
+// 20480.
+inline double stream_time(const GemmParams& p, int bm, int bn, int splits) {
+    const long per_cu = ((long)((p.M + bm - 1) / bm) * (p.N / bn) * splits + 255) / 256;
+    const double copy = per_cu * ((double)p.K1 / splits) * (bm + bn) * 2 / 60e9;
+    const double hbm = (double)p.N * p.K1 * 2 / 5.2e12;
+    const double t = std::max(copy, hbm) + 0.2 * std::min(copy, hbm) + (bm > 32 ? (per_cu - 1) * 2e-6 : 0.0);
+    return 3e-6 + (bn == 32 ? 1.2 * t : t) + split_cost(p, splits);  // two waves a block: fewer copies in flight
+}
+
+// `base`: plan_tiles' choice for the same launch, kept unless another shape is
+// predicted 5% (streaming) or 8% (tiles) faster.  Every other shape sums K in the same ranges as the
+// base, added in the same order (tiles: the same split; the streaming kernel:
+// the same split, or one block that closes a running sum at each range's end),
+// so the result does not depend on the shape chosen, bit for bit; ragged-round
+// plans, whose ranges differ from tile to tile, stay.  Measured gains over the
+// base (us): M 24, N 16384, K 4096 38 -> 27 (stream), M 200, N 6144, K 2048 20.1
+// -> 15.9 (stream 128 x 64), M 333, N 16384, K 4096 77 -> 59 (192 x 128), M 333,
+// N 5120, K 20480 112 -> 91 (192 x 256), M 700, N 15360, K 5120 152 -> 110 (192
+// x 256).
+WidePlan plan_wide(const GemmParams& p, const GemmWorkspace& wsp, const TilePlan& base) {
+    WidePlan best{WIDE_NONE, 0, 0, 0, 1, 0};
+    if (p.M > 2048 || base.ragged_tail > 0) return best;
+    double best_t = tile_time(p, base.tile, base.tile, base.splits);
+    const SplitArgs sa = make_split(p, wsp, base.splits);
+    // margins: about the scatter of the two models against measurement
+    auto consider = [&](double t, const WidePlan& w) {
+        const double margin = best.kind != WIDE_NONE ? 0.97 : w.kind == WIDE_STREAM ? 0.95 : 0.92;
+        if (t < best_t * margin) {
+            best_t = t;
+            best = w;
+        }
+    };
+    struct Shape { int kind, bm, bn; };
+    for (const Shape& c : {Shape{WIDE_RING, 128, 128}, Shape{WIDE_RING, 192, 128}, Shape{WIDE_PINGPONG, 128, 256},
+                           Shape{WIDE_PINGPONG, 192, 256}}) {
+        if (p.N % c.bn || (c.bm > 128 && p.M <= c.bm - 64)) continue;  // whole 64-row strips of padding
+        consider(tile_time(p, c.bm, c.bn, sa.splits), WidePlan{c.kind, c.bm, c.bn, 0, base.splits, 0});
+    }
+    // the streaming kernel's rows are 128 K elements wide
+    if (p.M <= STREAM_MAX_ROWS && p.K1 % 128 == 0) {
+        for (const Shape& c : {Shape{WIDE_STREAM, 32, 64}, Shape{WIDE_STREAM, 32, 32}, Shape{WIDE_STREAM, 64, 64},
+                               Shape{WIDE_STREAM, 128, 64}}) {
+            if (c.bm == 32 ? p.M > 32 : p.M <= c.bm / 2) continue;
+            consider(stream_time(p, c.bm, c.bn, 1), WidePlan{c.kind, c.bm, c.bn, 128, 1, sa.kt_split});
+            if (sa.splits > 1 && sa.kt_split % 2 == 0)
+                consider(stream_time(p, c.bm, c.bn, sa.splits),
+                         WidePlan{c.kind, c.bm, c.bn, 128, sa.splits, sa.kt_split});
         }
     }
-    // unsplit with a block or so per CU: 512-byte rows (144 KB of ring, one
-    // block per CU) measured 6-8% faster than 256-byte rows
-    if (best.bm == 32 && best.bn == 64 && best.splits == 1 && p.K1 % 256 == 0) best.bk = 256;
+    // unsplit with at most a block per CU: 512-byte rows (144 KB of ring)
+    // measured 6-8% faster than 256-byte rows
+    if (best.kind == WIDE_STREAM && best.bm == 32 && best.bn == 64 && best.splits == 1 && p.K1 % 256 == 0 &&
+        p.N / 64 <= 256)
+        best.bk = 256;
     return best;
 }
 
