@@ -89,6 +89,26 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const float* __restrict_
     }
 }
 
+// The shrink of rows another kernel has normalized (block y of a row takes
+// every gridDim.y-th group of G ranks)
+template <typename T, int MAXC, int G>
+__global__ __launch_bounds__(256) void row_shrink_kernel(const T* __restrict__ u, int d, RowShrink sh) {
+    __shared__ float red16[4][16];
+    const T* ur = u + (int64_t)blockIdx.x * d;
+    const int nc = d / 4;
+    f32x4 v[MAXC];
+#pragma unroll
+    for (int i = 0; i < MAXC; ++i) {
+        const int c = threadIdx.x + 256 * i;
+        const u32x2 raw = *(const u32x2*)(ur + 4 * min(c, nc - 1));
+        T e[4];
+        __builtin_memcpy(e, &raw, 8);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[i][r] = (float)e[r];
+    }
+    row_shrink<T, MAXC, G>(sh, (int)blockIdx.x, d, v, red16, (int)blockIdx.y, (int)gridDim.y);
+}
+
 // ---- LM head + argmax partials ----------------------------------------------
 // logits[b, v] = z[b] . E[v] for NB sequences at once, and per block the
 // (max, lowest index) of the rows it covered for each sequence, so the final
@@ -391,6 +411,29 @@ hipError_t launch_embed(int dtype, const int32_t* tok, const void* E, const void
     return hipGetLastError();
 }
 
+static int shrink_slices(const RowShrink& sh) {
+    return std::max(1, __builtin_popcount(sh.mask & 7u) * ((sh.rs + PB_LN_FEW_G - 1) / PB_LN_FEW_G));
+}
+
+hipError_t launch_row_shrink(int dtype, const void* u, const RowShrink& sh, int rows, int d, hipStream_t s) {
+    if (rows <= 0) return hipSuccess;
+    if (d % 4 || d > 256 * 4 * LN_MAXC) return hipErrorInvalidValue;
+    const dim3 grid(rows, shrink_slices(sh));
+#define PB_RS1(T, C) PB_LAUNCH((row_shrink_kernel<T, C, PB_LN_FEW_G>), grid, dim3(256), 0, s, (const T*)u, d, sh)
+#define PB_RS(T)                             \
+    do {                                     \
+        if (d <= 2048) PB_RS1(T, 2);         \
+        else if (d <= 4096) PB_RS1(T, 4);    \
+        else if (d <= 8192) PB_RS1(T, 8);    \
+        else PB_RS1(T, LN_MAXC);             \
+    } while (0)
+    if (dtype == 1) PB_RS(_Float16);
+    else PB_RS(__bf16);
+#undef PB_RS
+#undef PB_RS1
+    return hipGetLastError();
+}
+
 hipError_t launch_layernorm(int dtype, const float* x, int64_t in_mul, int64_t in_add,
                             const void* g, const void* b, void* out, bool out_f32, int rows,
                             int d, float eps, hipStream_t s, const RowShrink* shp) {
@@ -398,12 +441,12 @@ hipError_t launch_layernorm(int dtype, const float* x, int64_t in_mul, int64_t i
     if (d % 4 || d > 256 * 4 * LN_MAXC) return hipErrorInvalidValue;
     RowShrink sh{};
     if (shp && !out_f32) sh = *shp;
-    // a few rows (decode steps): the row's shrink groups of PB_LN_FEW_G ranks
-    // go to blocks of their own, so that the A reads spread over several CUs
-    // (many rows: groups of 16, one block per row)
-    const bool few = sh.Acat && rows <= 8;
-    int slices = 1;
-    if (few) slices = std::max(1, __builtin_popcount(sh.mask & 7u) * ((sh.rs + PB_LN_FEW_G - 1) / PB_LN_FEW_G));
+    // a few rows (decode steps, short prompts): the row's shrink groups of
+    // PB_LN_FEW_G ranks go to blocks of their own, so that the A reads spread
+    // over several CUs (12 rows, d 4096, q,k,v rank 16: 18.5 us in one block per
+    // row); many rows: groups of 16, one block per row
+    const bool few = sh.Acat && rows <= ROW_SHRINK_APART;
+    const int slices = few ? shrink_slices(sh) : 1;
 #define PB_LN2(T, F, C, SH, G, AH)                                                                 \
     PB_LAUNCH((layernorm_kernel<T, F, C, SH, G, AH>), dim3(rows, slices), dim3(256), 0, s, x, in_mul, \
               in_add, (const T*)g, (const T*)b, out, d, eps, sh)
