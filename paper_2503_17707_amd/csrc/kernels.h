@@ -92,9 +92,9 @@ hipError_t launch_layernorm(int dtype, const float* x, int64_t in_mul, int64_t i
                             const void* g, const void* b, void* out, bool out_f32, int rows,
                             int d, float eps, hipStream_t s, const RowShrink* sh = nullptr);
 
-// The row-wise LoRA shrink alone, of rows u [rows, d] (dt) already normalized:
-// the same values the kernels that produce the rows would write, spread over
-// several blocks per row.
+// The row-wise LoRA shrink alone, of finished rows u [rows, d] (dt; LayerNorm
+// rows: the same values the kernels that produce them would write; attention
+// rows for o), spread over several blocks per row.
 hipError_t launch_row_shrink(int dtype, const void* u, const RowShrink& sh, int rows, int d, hipStream_t s);
 // Rows up to which the shrink's rank groups go to blocks of their own.
 constexpr int ROW_SHRINK_APART = 64;

@@ -922,16 +922,16 @@ int enqueue_forward(pb_model* m, int B, int T, bool use_lora, uint32_t lora_unio
     const bool qkv_lora = use_lora && (lora_union & (PB_LORA_Q | PB_LORA_K | PB_LORA_V));
     const bool o_lora = use_lora && (lora_union & PB_LORA_O);
     // Up to 1024 tokens the q/k/v LoRA shrink rides on the kernel that writes
-    // the LayerNorm rows (row-wise dot products; for a handful of rows, decode
-    // steps, each row's 16-rank groups go to blocks of their own so that the A
-    // reads spread over several CUs); for more tokens it is a GEMM.
+    // the LayerNorm rows (row-wise dot products; up to 64 rows each row's
+    // groups of four ranks go to blocks of their own so that the A reads spread
+    // over several CUs); for more tokens it is a GEMM.
     const bool fuse_shrink = qkv_lora && N <= ROW_SHRINK_MAX_TOKENS;
     auto row_shrink_args = [&](int layer) {
         pb::RowShrink sh{};
         if (fuse_shrink) {
             sh.Acat = m->at(a.loraA) + (size_t)layer * a.loraA_layer;
             sh.row_slot = rowslot; sh.slot_scale = sscale; sh.Z = z;
-            sh.rs = a.rs; sh.kw = kw; sh.mask = lora_union & 7u;
+            sh.rs = a.rs; sh.kw = kw; sh.zcols = 3 * kw; sh.mask = lora_union & 7u;
         }
         return sh;
     };
@@ -989,7 +989,23 @@ int enqueue_forward(pb_model* m, int B, int T, bool use_lora, uint32_t lora_unio
                 HIP_TRY(pb::launch_decode_attention(dt, qkv, kvl, (int64_t)a.kv_seq, B, H, hd, pos0, attn, s));
             }
         }
-        if (o_lora) {
+        // o's shrink of 3 to 64 rows: row-wise dot products over the row's own
+        // slot in one launch; the GEMM reads every slot's A and at these sizes is
+        // a split tile with a reduce launch behind it (per layer 2 to 6 us more).
+        // With the row kernel for q,k,v,o adapters: OPT-1.3B prefill of 61 tokens
+        // 1977 -> 1842 us, of 5 1531 -> 1448; four layers of d 4096, 16 decode
+        // steps: 8 sequences 12.31 -> 12.06 ms, 12 13.05 -> 12.72, 4 11.67 ->
+        // 11.57.  1 and 2 rows: the GEMV is as fast (9.09 against 9.10, 9.91
+        // against 9.89).  Past 64 rows, where the q, k, v shrink
+        // changes too, the GEMM's tiles share their A reads over the rows.
+        if (o_lora && N > 2 && N <= pb::ROW_SHRINK_APART) {
+            Timed t(m, PB_K_LORA_SHRINK);
+            pb::RowShrink sh{};
+            sh.Acat = Aq + 3 * (size_t)kw * d * 2;
+            sh.row_slot = rowslot; sh.slot_scale = sscale; sh.Z = z + 3 * (size_t)kw * 2;
+            sh.rs = a.rs; sh.kw = kw; sh.zcols = kw; sh.mask = 1u;
+            HIP_TRY(pb::launch_row_shrink(dt, attn, sh, N, d, s));
+        } else if (o_lora) {
             Timed t(m, PB_K_LORA_SHRINK);
             pb::GemmParams p{};
             p.X = attn; p.ldx = d; p.W = Aq + 3 * (size_t)kw * d * 2; p.ldw = d; p.M = N; p.N = kw; p.K1 = d;

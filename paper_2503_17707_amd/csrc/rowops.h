@@ -17,7 +17,8 @@ struct RowShrink {
     const float* slot_scale; // [16]
     void* Z;                 // [M][4 kw] (dt)
     int rs, kw;
-    uint32_t mask;           // targets q=1, k=2, v=4
+    int zcols;               // columns of Z written: kw per target covered (q, k, v: 3 kw)
+    uint32_t mask;           // targets q=1, k=2, v=4 (1 alone with Acat and Z at o's part: o)
 };
 
 // One LayerNorm output before rounding: (v - mean) rstd g + b, with the
@@ -216,7 +217,7 @@ __device__ __forceinline__ void row_shrink(const RowShrink& sh, int m, int d, co
     T* zr = (T*)sh.Z + (int64_t)m * 4 * sh.kw;
     // zero every column outside the row's own slot block of an active target
     if (slice == 0)
-        for (int c = tid; c < 3 * sh.kw; c += 256) {
+        for (int c = tid; c < sh.zcols; c += 256) {
             const int t = c / sh.kw, cc = c % sh.kw;
             const bool own = slot >= 0 && ((sh.mask >> t) & 1u) && cc >= slot * sh.rs && cc < (slot + 1) * sh.rs;
             if (!own) zr[c] = (T)0.f;
