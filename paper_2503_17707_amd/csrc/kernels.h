@@ -131,7 +131,8 @@ hipError_t launch_lora_pack(int dtype, const void* staging, size_t staging_layer
 // Attention weights of every layer, [Wq|Wk|Wv|Wo] as four [d, d] matrices at
 // src + layer * src_stride (bytes), written to dst + layer * dst_stride (the
 // same place allowed): targets in merge_mask as dt(src + scale * (slot's B [d,
-// rs]) (slot's A [rs, d])), rounded once, targets in copy_mask unchanged, the
+// rs]) (slot's A [rs, d])), the product summed in fp32 and the rest rounded once
+// for f16, to fp32 and then to bf16 for bf16, targets in copy_mask unchanged, the
 // others not written (misc.hip).  A, B: the packed slot arrays of all layers.
 struct MergeParams {
     const char* src; int64_t src_stride;

@@ -352,11 +352,25 @@ __global__ __launch_bounds__(256) void lora_pack_kernel(const T* __restrict__ st
 // rows of one matrix: the slot's A columns (Acat [kw][d], rows slot*rs ..) are
 // read once for all of its rows, whose B values (Bcat [d][kw], columns slot*rs
 // ..) are the same for the whole block.  The rank-rs product is summed in
-// fp32, ranks in order, then W + s * product is rounded once to dt.  HBM-bound:
+// fp32, ranks in order, then added and rounded by fma_round_once.  HBM-bound:
 // src read, W written (one row per thread re-read A from L2 for every row and
 // took 12.2 us per 2048 x 2048 matrix, 1.4 TB/s; 805 MB of an OPT-1.3B switch
 // took 586 us plus 293 for the restoring copy).
 constexpr int MERGE_ROWS = 8;
+
+// w + s a in the storage type, the same rounding for every element wherever it
+// sits in a thread's block.  f16: rounded once, by the mixed-precision
+// multiply-add (left to itself the compiler takes it for some elements only and
+// rounds the others to fp32 first).  bf16 has no such instruction: a fused
+// multiply-add in fp32, then the conversion.
+__device__ __forceinline__ _Float16 fma_round_once(float s, float a, _Float16 w) {
+    _Float16 y;
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[0,0,1]" : "=v"(y) : "v"(s), "v"(a), "v"(w));
+    return y;
+}
+__device__ __forceinline__ __bf16 fma_round_once(float s, float a, __bf16 w) {
+    return (__bf16)__builtin_fmaf(s, a, (float)w);
+}
 
 template <typename T>
 __global__ __launch_bounds__(256) void lora_merge_kernel(MergeParams p) {
@@ -393,7 +407,7 @@ __global__ __launch_bounds__(256) void lora_merge_kernel(MergeParams p) {
             T w[8];
             __builtin_memcpy(w, &raw[r], 16);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) w[e] = (T)__builtin_fmaf(p.scale, acc[r][e], (float)w[e]);
+            for (int e = 0; e < 8; ++e) w[e] = fma_round_once(p.scale, acc[r][e], w[e]);
             __builtin_memcpy(&raw[r], w, 16);
         }
     }
