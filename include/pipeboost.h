@@ -242,7 +242,8 @@ int pb_prefill_stage(pb_model* m, const int32_t* tokens, int32_t B, int32_t T, c
 
 /* Merged LoRA (Section 4.3.2): fold adapter slot `slot` into the device base
  * weights of every layer, W_t = dt(W_t + scale * B_t A_t) for each of its
- * targets (fp32 product, one rounding), on the compute stream after every
+ * targets (fp32 product; one rounding in f16, to fp32 and then to bf16 in
+ * bf16), on the compute stream after every
  * layer's copy; blocks until done.  Afterwards the base weights are the merged
  * model: every sequence runs with adapter -1 (a prefill or decode naming any
  * adapter fails with PB_ESTATE) and no LoRA work remains on the hot path.
@@ -252,7 +253,9 @@ int pb_prefill_stage(pb_model* m, const int32_t* tokens, int32_t B, int32_t T, c
  * first restores them from it (an adapter switch: the result is bit-identical
  * to merging onto freshly streamed weights); without, that merge fails with
  * PB_ESTATE.  Requires an attached slot and a prior pb_stream_layers
- * (PB_ESTATE). */
+ * (PB_ESTATE).  After a merge or unmerge that failed (PB_EHIP) no adapter is
+ * merged and the base weights are undefined: prefills fail with PB_ESTATE until
+ * a merge or unmerge (with merge_shadow) or pb_stream_layers has succeeded. */
 int pb_merge_lora(pb_model* m, int32_t slot);
 
 /* Restore the unmerged base weights from the shadow copy (blocks until done).

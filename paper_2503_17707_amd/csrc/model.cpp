@@ -296,7 +296,10 @@ struct pb_model {
     bool ring_busy[STAGE_SLOTS] = {};
     int ring_next = 0;
     int merged_slot = -1;  // adapter merged into the device base weights (-1: none)
-    uint32_t merged_mask = 0;  // its targets (the slot may be attached anew meanwhile)
+    // targets whose device weights may differ from the unmerged ones: those of the
+    // merged adapter (its slot may be attached anew meanwhile), or, with none
+    // merged, those that a failed merge or unmerge may have left half-written
+    uint32_t dirty_mask = 0;
     bool shadow_valid = false;  // the shadow holds this load's unmerged attention weights
     // decode state: sequences of the last prefill, their length so far
     int dec_B = 0, dec_len = 0, dec_steps = 0;
@@ -721,6 +724,7 @@ int pb_stream_layers(pb_model* m, const int32_t* layer_order, int32_t n_layers,
     if (m->copy2) HIP_TRY(hipStreamWaitEvent(m->copy2, m->ev_load0, 0));
     m->last_load_bytes = (double)gb + (double)n_layers * (double)lb;
     m->merged_slot = -1;  // the base weights arrive unmerged
+    m->dirty_mask = 0;
     m->shadow_valid = false;
     if (all_pinned) {
         // every copy is a DMA from locked pages: enqueue them all now
@@ -785,6 +789,7 @@ int pb_poison_weights(pb_model* m, int32_t value) {
     m->streamed = false;
     m->dec_B = 0;
     m->merged_slot = -1;
+    m->dirty_mask = 0;
     m->shadow_valid = false;
     return PB_OK;
 }
@@ -1158,6 +1163,9 @@ static int run_forward(pb_model* m, const int32_t* tokens, int32_t B, int32_t T,
                        bool decode, const uint8_t* has_kv = nullptr, const Stage* st = nullptr) {
     const pb_config& c = m->cfg;
     const int N = B * T;
+    if (m->merged_slot < 0 && m->dirty_mask)
+        return fail(PB_ESTATE, "a merge or unmerge failed and left the base weights undefined: %s",
+                    m->shadow_valid ? "merge, unmerge or stream them again" : "stream them again");
     for (int i = 0; i < N; ++i)
         if (tokens[i] < 0 || tokens[i] >= c.vocab) return fail(PB_EINVAL, "token %d at %d outside [0, %d)", tokens[i], i, c.vocab);
     bool use_lora = false;
@@ -1356,6 +1364,8 @@ extern "C" int pb_merge_lora(pb_model* m, int32_t slot) {
     if (m->merged_slot >= 0 && !c.merge_shadow)
         return fail(PB_ESTATE, "adapter %d is already merged; stream the base layers again first (or keep a merge shadow)",
                     m->merged_slot);
+    if (m->dirty_mask && !m->shadow_valid)
+        return fail(PB_ESTATE, "a merge failed and left the base weights undefined: stream them again");
     const ArenaLayout& a = m->lay;
     hipStream_t s = m->compute;
     // every layer (and the adapter) must have landed before it is rewritten
@@ -1364,13 +1374,11 @@ extern "C" int pb_merge_lora(pb_model* m, int32_t slot) {
         if (int rc = wait_recorded(m, l)) return rc;
         HIP_TRY(hipStreamWaitEvent(s, m->ev_layer[l], 0));
     }
-    // a switch reads the unmerged weights from the shadow: targets that only
-    // the previous adapter changed go back unchanged in the same launch
-    const bool from_shadow = c.merge_shadow && m->merged_slot >= 0;
-    if (c.merge_shadow && !from_shadow && !m->shadow_valid) {
+    // over weights that are not the unmerged ones a merge reads those from the
+    // shadow: targets that it does not cover go back unchanged in the same launch
+    const bool from_shadow = m->dirty_mask != 0;
+    if (c.merge_shadow && !m->shadow_valid)
         if (int rc = copy_shadow(m, true)) return rc;
-        m->shadow_valid = true;
-    }
     const uint32_t mask = m->slot_mask[slot];
     pb::MergeParams p{};
     char* layers = m->at(a.layers) + a.attn_w;  // Wq|Wk|Wv|Wo, consecutive [d, d] matrices (d a multiple of 128)
@@ -1383,24 +1391,32 @@ extern "C" int pb_merge_lora(pb_model* m, int32_t slot) {
     p.layers = c.n_layers; p.d = c.d_model; p.kw = a.kw; p.rs = a.rs; p.slot = slot;
     p.scale = m->slot_scale[slot];
     p.merge_mask = mask;
-    p.copy_mask = from_shadow ? m->merged_mask & ~mask : 0u;
+    p.copy_mask = m->dirty_mask & ~mask;
+    // until the launch has ended without an error no adapter is merged, and all
+    // that it writes counts as written
     m->merged_slot = -1;
+    m->dirty_mask |= mask;
     m->dec_B = 0;  // a KV cache from before the merge belongs to another model
-    HIP_TRY(pb::launch_lora_merge(c.dtype, p, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    const hipError_t merge_launch = pb::launch_lora_merge(c.dtype, p, s);
+    const hipError_t merge_end = hipStreamSynchronize(s);
+    if (merge_end == hipSuccess) m->shadow_valid = c.merge_shadow != 0;  // also after a failed launch
+    HIP_TRY(merge_launch);
+    HIP_TRY(merge_end);
     m->merged_slot = slot;
-    m->merged_mask = mask;
+    m->dirty_mask = mask;
     return PB_OK;
 }
 
 extern "C" int pb_unmerge_lora(pb_model* m) {
     if (!m) return fail(PB_EINVAL, "model is NULL");
     if (!m->cfg.merge_shadow) return fail(PB_ESTATE, "the model keeps no merge shadow");
-    if (m->merged_slot < 0) return fail(PB_ESTATE, "no adapter is merged");
+    if (!m->dirty_mask) return fail(PB_ESTATE, "no adapter is merged");
+    if (!m->shadow_valid) return fail(PB_ESTATE, "the shadow was not written: stream the base layers again");
+    m->merged_slot = -1;  // until the copy has ended the weights are neither model
+    m->dec_B = 0;
     if (int rc = copy_shadow(m, false)) return rc;
     HIP_TRY(hipStreamSynchronize(m->compute));
-    m->merged_slot = -1;
-    m->dec_B = 0;
+    m->dirty_mask = 0;
     return PB_OK;
 }
 
