@@ -464,6 +464,12 @@ void gemm_pingpong_kernel(GemmParams p, SplitArgs sa) {
 // and a reduce against 16.6).  HBM-bound for large N, by its fixed ~3 us for
 // small ones.  An unsplit launch still adds the K ranges of plan_tiles' split
 // one after another (the same result as its partials and reduce, bit for bit).
+// Up to GEMV_MAX_ROWS rows, which the GEMV's dot products serve as well, a
+// chain of MFMA sums ends after 128 elements and the running sum keeps the
+// rounding errors of its additions (two-sum).  Chains as long as a K range lost
+// more than the dot products' short ones (relative error of the sums, K 2048 ..
+// 36864: 1.5e-7 .. 4.6e-7 with a workspace, up to 1.2e-6 without, the GEMV's
+// 0.9e-7 .. 1.3e-7, these 0.8e-7 .. 1.0e-7).
 // The base K ranges are independent of the LoRA segment (B = 0 stays
 // bit-identical to the base), whose few columns are read
 // straight into registers: the first 64, requested ahead of the ring, have
@@ -560,6 +566,44 @@ __global__ __launch_bounds__(64 * WGM * WGN) void stream_kernel(GemmParams p, Sp
         }
     };
 
+    // few rows: only the first 16 tokens exist; low holds the rounding errors of sum
+    constexpr bool FEW = BM == 32;
+    const bool few = FEW && p.M <= GEMV_MAX_ROWS;
+    f32x4 low[NF];
+#pragma unroll
+    for (int i = 0; i < NF; ++i) low[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto compute_few = [&](int stage) {
+        const uint8_t* s = smem + stage * STAGE;
+#pragma unroll
+        for (int h = 0; h < BKE / 128; ++h) {
+            f32x4 c[NF];
+#pragma unroll
+            for (int i = 0; i < NF; ++i) c[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kk = 4 * h; kk < 4 * h + 4; ++kk) {
+                const int ch = kk * 4 + lg;
+                const vec8 b = as_vec8<T>(*(const u32x4*)(s + lr * RB + ((ch ^ lr) << 4)));
+#pragma unroll
+                for (int i = 0; i < NF; ++i) {
+                    const int row = BM + wn * WN + i * 16 + lr;
+                    c[i] = Mfma<T>::mma(as_vec8<T>(*(const u32x4*)(s + row * RB + ((ch ^ (row & 15)) << 4))), b, c[i]);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < NF; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float x = sum[i][0][r], y = c[i][r], t = x + y, yy = t - x;
+                    low[i][r] += (x - (t - yy)) + (y - yy);
+                    sum[i][0][r] = t;
+                }
+        }
+    };
+    auto step = [&](int stage) {
+        if (few) compute_few(stage);
+        else compute(stage);
+    };
+
     // LoRA segment of this block's output group (last split): operands of one
     // 32-wide step straight from global memory
     int nk2 = 0;
@@ -602,13 +646,13 @@ __global__ __launch_bounds__(64 * WGM * WGN) void stream_kernel(GemmParams p, Sp
         wait_vmcnt<(S - 2) * NL>();
         __syncthreads();  // stage st visible to all waves; the stage before it free
         issue(t0 + t + S - 1, st == 0 ? S - 1 : st - 1);
-        compute(st);
+        step(st);
         st = st == S - 1 ? 0 : st + 1;
     }
     for (; t < n; ++t) {
         wait_vmcnt<0>();
         __syncthreads();
-        compute(st);
+        step(st);
         st = st == S - 1 ? 0 : st + 1;
     }
     if (nk2 > 0) {
@@ -621,7 +665,15 @@ __global__ __launch_bounds__(64 * WGM * WGN) void stream_kernel(GemmParams p, Sp
             mul2(l1);
         }
     }
-    close_range();
+    if (few) {
+#pragma unroll
+        for (int i = 0; i < NF; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)  // acc: the LoRA columns; an overflowed sum has a NaN for its error
+                sum[i][0][r] += fabsf(sum[i][0][r]) < INFINITY ? low[i][r] + acc[i][0][r] : acc[i][0][r];
+    } else {
+        close_range();
+    }
     TileJob jb;
     jb.partial = sa.splits > 1;
     jb.pbase = sa.ws + (int64_t)split * p.M * p.N;
@@ -863,7 +915,7 @@ template <typename T, int EPI, int ROLE>
 hipError_t launch_tiles(const GemmParams& p, const GemmWorkspace& wsp, hipStream_t s) {
     const TilePlan tp = plan_for_role(ROLE, p, wsp);
     if constexpr (ROLE != 4) {
-        const WidePlan w = plan_wide(p, wsp, tp);
+        const WidePlan w = p.M <= GEMV_MAX_ROWS ? plan_few(p, wsp) : plan_wide(p, wsp, tp);
         if (w.kind != WIDE_NONE) return launch_wide<T, EPI, ROLE>(p, wsp, w, s);
     }
     if constexpr (ROLE == 4) {
@@ -1033,15 +1085,9 @@ hipError_t launch_gemm(int dtype, int role, int epi, const GemmParams& p, const 
         return hipErrorInvalidValue;
     const int expect[5] = {EPI_QKV, EPI_RESID, EPI_RELU, EPI_RESID, EPI_SHRINK};
     if (role < 0 || role > 4 || expect[role] != epi) return hipErrorInvalidValue;
-    // The GEMV's fp32 dot products cost arithmetic per row (N 8192, K 2048: 7.6
-    // us for 1 row, 13.1 for 4, 22.5 for 8), the streaming kernel's matrix
-    // products do not (10.2 us up to 16 rows): the GEMV takes 1 and 2 rows, 3
-    // and 4 for few features, where the streaming kernel would need a reduce
-    // launch (N 2048, K 2048: 6.1 us against 8.1; N 5120, K 20480: 40.4 against
-    // 42.3; not where the LayerNorm that follows is that reduce), and up to 8
-    // where that kernel does not apply (the LoRA shrink, K not a multiple of 128).
-    const bool gemv = p.M <= 2 || (p.M <= 4 && p.N <= 5120 && !p.ln_out) ||
-                      (p.M <= GEMV_MAX_ROWS && (role == 4 || p.K1 % 128));
+    // few rows: the GEMV unless the streaming kernel is planned (never for the
+    // LoRA shrink, whose epilogue it does not know)
+    const bool gemv = p.M <= GEMV_MAX_ROWS && (role == 4 || plan_few(p, wsp).kind == WIDE_NONE);
     if (PB_GEMM_GEMV && gemv)
         return dtype == 1 ? launch_gemv_typed<_Float16>(role, p, s) : launch_gemv_typed<__bf16>(role, p, s);
     if (dtype == 1) return launch_typed<_Float16>(role, p, wsp, s);

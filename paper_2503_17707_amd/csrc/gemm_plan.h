@@ -6,6 +6,7 @@
 #pragma once
 
 #include <algorithm>
+#include <cmath>
 
 #include "kernels.h"
 
@@ -312,6 +313,12 @@ inline double stream_time(const GemmParams& p, int bm, int bn, int splits) {
     return 3e-6 + (bn == 32 ? 1.2 * t : t) + split_cost(p, splits);  // two waves a block: fewer copies in flight
 }
 
+// K elements per ring stage of 32-row blocks: unsplit with at most a block per
+// CU, 512-byte rows (144 KB of ring) measured 6-8% faster than 256-byte rows.
+inline int wide_row_stage(const GemmParams& p, int bn, int splits) {
+    return bn == 64 && splits == 1 && p.K1 % 256 == 0 && p.N / 64 <= 256 ? 256 : 128;
+}
+
 // `base`: plan_tiles' choice for the same launch, kept unless another shape is
 // predicted 5% (streaming) or 8% (tiles) faster.  Every other shape sums K in the same ranges as the
 // base, added in the same order (tiles: the same split; the streaming kernel:
@@ -324,7 +331,7 @@ inline double stream_time(const GemmParams& p, int bm, int bn, int splits) {
 // x 256).
 WidePlan plan_wide(const GemmParams& p, const GemmWorkspace& wsp, const TilePlan& base) {
     WidePlan best{WIDE_NONE, 0, 0, 0, 1, 0};
-    if (p.M > 2048 || base.ragged_tail > 0) return best;
+    if (p.M <= GEMV_MAX_ROWS || p.M > 2048 || base.ragged_tail > 0) return best;
     double best_t = tile_time(p, base.tile, base.tile, base.splits);
     const SplitArgs sa = make_split(p, wsp, base.splits);
     // margins: about the scatter of the two models against measurement
@@ -352,11 +359,65 @@ WidePlan plan_wide(const GemmParams& p, const GemmWorkspace& wsp, const TilePlan
                          WidePlan{c.kind, c.bm, c.bn, 128, sa.splits, sa.kt_split});
         }
     }
-    // unsplit with at most a block per CU: 512-byte rows (144 KB of ring)
-    // measured 6-8% faster than 256-byte rows
-    if (best.kind == WIDE_STREAM && best.bm == 32 && best.bn == 64 && best.splits == 1 && p.K1 % 256 == 0 &&
-        p.N / 64 <= 256)
-        best.bk = 256;
+    if (best.kind == WIDE_STREAM && best.bm == 32) best.bk = wide_row_stage(p, best.bn, best.splits);
+    return best;
+}
+
+// Time of a GEMV launch of at most GEMV_MAX_ROWS rows (gemv_kernel: a wave
+// takes 4 features x K / KW): the weights at 5.8 TB/s, or the waves' dot products
+// (208 cycles per row and 512 elements) and lane sums (400 per row) over the
+// chip's 1024 SIMDs, rows in groups of 4 or 8; a LayerNorm that follows is a
+// pass of its own.  Fitted, as few_stream_time, to the times of the projections of
+// d_model 768 .. 12288 with 3 and 8 rows (mean error 8%).
+inline double gemv_time(const GemmParams& p) {
+    const int rows = p.M <= 1 ? 1 : p.M <= 2 ? 2 : p.M <= 4 ? 4 : 8, kw = p.K1 >= 4096 ? 8 : 4;
+    const double dots = (double)p.N / 4 * kw * rows * (208.0 * p.K1 / kw / 512 + 400.0) / (1024 * 2.1e9);
+    return 4.6e-6 + std::max(dots, (double)p.N * p.K1 * 2 / 5.8e12) + split_cost(p, 1);
+}
+
+// ... and of a stream launch of so few rows in 32 x bn blocks: copies into LDS
+// at 75 GB/s per CU, cold weights at 7.2 TB/s (less with fewer blocks than CUs),
+// half of the shorter one left over, and a reduce that is mostly launch.
+inline double few_stream_time(const GemmParams& p, int bn, int splits) {
+    const long blocks = (long)(p.N / bn) * splits, per_cu = (blocks + 255) / 256;
+    const double copy = per_cu * ((double)p.K1 / splits) * (32 + bn) * 2 / 75e9;
+    const double hbm = (double)p.N * p.K1 * 2 / 7.2e12 / std::pow(std::min(1.0, (double)blocks / 256), 0.4);
+    const double t = std::max(copy, hbm) + 0.5 * std::min(copy, hbm);
+    return 3.7e-6 + (bn == 32 ? 1.03 * t : t) +
+           (splits > 1 ? 2.0 * p.M * p.N * 4 * splits / 8e12 + 3e-6 : split_cost(p, 1));
+}
+
+// Launch of at most GEMV_MAX_ROWS rows: WIDE_NONE is the GEMV.  Its fp32 dot
+// products cost arithmetic per row, the streaming kernel's matrix products do
+// not (N 8192, K 2048: 13.3 us for 3 rows and 22.2 for 8 against 10.9; N 27648, K
+// 9216: 94 and 175 against 92); the GEMV keeps 1 and 2 rows, few features (N 2048,
+// K 2048, 3 rows: 6.3 against 8.2) and long weight rows of 3 and 4 (N 9216, K 36864:
+// 119 against 125).  The faster of the two and of the splits by the two models
+// above was within 0.6% of the fastest in the mean, 8% at worst, over those
+// shapes.  K ranges are whole ring stages: no other launch has to give the same
+// bits.  Operands that are not 16-byte aligned are the GEMV's, which takes them.
+// Sums of fewer than 768 products are too: the GEMV's error is smaller there
+// (bf16, K 512: 6.2e-8 relative against 6.4e-8; K 768: 6.5e-8 against 6.4e-8, K
+// 8192: 8.8e-8 against 8.6e-8, f16 alike).
+WidePlan plan_few(const GemmParams& p, const GemmWorkspace& wsp) {
+    WidePlan best{WIDE_NONE, 0, 0, 0, 1, 0};
+    if (p.M <= 2 || p.M > GEMV_MAX_ROWS || p.K1 % 128 || p.K1 < 768 ||
+        (((uintptr_t)p.X | (uintptr_t)p.W | (uintptr_t)(p.ldx * 2) | (uintptr_t)(p.ldw * 2)) & 15))
+        return best;
+    double best_t = gemv_time(p);
+    const int nk = p.K1 / BK;
+    for (int bn : {64, 32})
+        for (int s = 1; s <= 8; ++s) {
+            const int kt = ((nk + s - 1) / s + 1) / 2 * 2, splits = (nk + kt - 1) / kt;
+            if (splits != s || (s > 1 && (nk / s < PB_GEMM_MIN_KT || !wsp.ws ||
+                                          (double)p.M * p.N * 4 * s > (double)wsp.bytes)))
+                continue;
+            const double t = few_stream_time(p, bn, s);
+            if (t < best_t * 0.98) {  // the simpler launch on near ties
+                best_t = t;
+                best = {WIDE_STREAM, 32, bn, wide_row_stage(p, bn, s), s, kt};
+            }
+        }
     return best;
 }
 

@@ -1,7 +1,9 @@
-// Host-side check of the launches plan_wide adds to the square tiles: over the
-// projections of several widths and ragged row counts from 3 to 2048, every
-// output tile is covered by exactly its K ranges (each stage or K tile once),
-// partials fit the workspace, and the shapes are ones the launcher knows.
+// Host-side check of the launches that plan_wide adds to the square tiles and
+// plan_few to the GEMV: over the projections of several widths and ragged row
+// counts from 1 to 2048, every output tile is covered by exactly its K ranges
+// (each stage or K tile once), partials fit the workspace, and the shapes are
+// ones the launcher knows; 1 and 2 rows and unaligned operands stay the GEMV's,
+// and no launch of up to 8 rows is a plain tile.
 // Test infrastructure: builds the library's planning header for the host.
 #include "gemm_plan.h"
 
@@ -67,17 +69,32 @@ void run(int role, int M, int N, int K, int group, bool ln, size_t ws_bytes) {
     static char dummy;
     if (ln) p.ln_out = &dummy;
     const pb::GemmWorkspace ws{ws_bytes ? (void*)0x40000000 : nullptr, ws_bytes};
+    p.ldx = p.ldw = K;
+    const bool few = M <= pb::GEMV_MAX_ROWS;
     const pb::TilePlan base = pb::plan_for_role(role, p, ws);
-    const pb::WidePlan w = pb::plan_wide(p, ws, base);
+    const pb::WidePlan w = few ? pb::plan_few(p, ws) : pb::plan_wide(p, ws, base);
+    if (few) {
+        CHECK(pb::plan_wide(p, ws, base).kind == pb::WIDE_NONE, "few rows in a tile");
+        CHECK(w.kind == pb::WIDE_NONE || (w.kind == pb::WIDE_STREAM && w.bm == 32), "kernel of few rows");
+        CHECK(M > 2 || w.kind == pb::WIDE_NONE, "1 and 2 rows");
+        pb::GemmParams q = p;
+        q.X = (const void*)0x1002;
+        CHECK(pb::plan_few(q, ws).kind == pb::WIDE_NONE, "unaligned X");
+        q = p;
+        q.W = (const void*)0x1008;
+        CHECK(pb::plan_few(q, ws).kind == pb::WIDE_NONE, "unaligned W");
+    }
     ++launches;
     char key[48];
     std::snprintf(key, sizeof key, "%d:%dx%dk%d/%d", w.kind, w.bm, w.bn, w.bk, w.splits);
     ++seen[key];
     if (w.kind == pb::WIDE_NONE) return;
-    // the sum's K ranges are the base's
-    const pb::SplitArgs sa = pb::make_split(p, ws, base.splits);
-    CHECK(base.ragged_tail == 0 && (w.splits == 1 || pb::make_split(p, ws, w.splits).kt_split == sa.kt_split), "ranges");
-    CHECK(w.kind == pb::WIDE_STREAM ? w.kt == sa.kt_split : w.splits == base.splits, "order of the sum");
+    if (!few) {  // the sum's K ranges are the base's
+        const pb::SplitArgs sa = pb::make_split(p, ws, base.splits);
+        CHECK(base.ragged_tail == 0 && (w.splits == 1 || pb::make_split(p, ws, w.splits).kt_split == sa.kt_split),
+              "ranges");
+        CHECK(w.kind == pb::WIDE_STREAM ? w.kt == sa.kt_split : w.splits == base.splits, "order of the sum");
+    }
     CHECK(w.splits == 1 || (ws.ws && (double)w.splits * M * N * 4 <= (double)ws_bytes), "workspace");
     if (w.kind == pb::WIDE_STREAM) {
         if (w.bm == 128 && w.bn == 64 && w.bk == 128) check_stream<128, 64, 128>(p, w);
@@ -102,7 +119,7 @@ void run(int role, int M, int N, int K, int group, bool ln, size_t ws_bytes) {
 int main() {
     for (int d : {128, 256, 384, 2048, 2176, 4096, 5120, 9216})
         for (int F : {4 * d, 4 * d + 64})
-            for (int M : {3, 8, 9, 16, 31, 32, 33, 61, 64, 65, 100, 128, 129, 200, 256, 257, 333, 385, 512, 513, 700, 1000, 2000,
+            for (int M : {1, 2, 3, 4, 5, 8, 9, 16, 31, 32, 33, 61, 64, 65, 100, 128, 129, 200, 256, 257, 333, 385, 512, 513, 700, 1000, 2000,
                           2048, 2049})
                 for (size_t ws : {(size_t)0, (size_t)16 << 20, (size_t)1 << 30}) {
                     run(0, M, 3 * d, d, d, false, ws);
