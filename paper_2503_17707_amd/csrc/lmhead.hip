@@ -8,7 +8,9 @@
 // nothing is rounded that the dot products kept:
 //   bf16: z = h + l + m, 8 + 8 + 8 significant bits;
 //   f16:  z = 2^e (h + 2^-11 l + 2^-22 m), |h| <= 1, 11 bits each (the power
-//         of two keeps the terms inside f16's range whatever the row's scale).
+//         of two keeps the terms inside f16's range whatever the row's scale;
+//         elements below about 2^-25 of the row's largest lose bits, all of them
+//         below 2^-46 of it).
 // Products are exact in fp32 and accumulate in fp32, one accumulator per term,
 // the first term's sums of 128 products added up with their rounding errors
 // kept (two-sum): one long chain of fp32 additions would lose more than the
@@ -259,9 +261,12 @@ hipError_t launch_typed(const float* z, int B, const T* E, int V, int d, float* 
 // of its single-sequence passes for up to 16 sequences.  Measured (vocab
 // 50272): d 2048, 2 sequences 55 us against 72; d 4096, 2: 105 against 68,
 // 3: 107 against 137, 12: 107 against 389; d 9216, 2: 209 against 141, 3: 209
-// against 279.
+// against 279.  Narrow rows stay with the dot products, whose error is smaller
+// there (f16, relative: d 128 7.4-7.9e-8 against 7.6-9.3e-8, d 256 7.7-8.7e-8
+// against 7.7-9.0e-8; d 512 8.1-8.9e-8 against 7.7-8.6e-8, d 4096 1.0-1.1e-7 against
+// 7.7-8.9e-8).
 bool lm_head_use_mfma(int B, int V, int d) {
-    if (d % 128 || (int64_t)V * d >= ((int64_t)1 << 31)) return false;
+    if (d < 512 || d % 128 || (int64_t)V * d >= ((int64_t)1 << 31)) return false;
     return B >= 3 || (B == 2 && (d <= 2048 || d > 10240));
 }
 

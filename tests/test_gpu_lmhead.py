@@ -1,8 +1,8 @@
-"""The matrix-unit LM head (several sequences) through prefills of one layer:
-sequence counts at the edges of its 16- and 32-sequence groups, vocabularies
-ragged against its 64-row blocks and against 16-byte stores, the narrowest K
-(one stage) and a longer one; logits against the oracle, tokens the first
-maximum of the returned logits."""
+"""The LM head of several sequences through prefills of one layer, on the matrix
+units (d from 512 on) and on the dot products: sequence counts at the edges of
+the matrix-unit head's 16- and 32-sequence groups, vocabularies ragged against
+its 64-row blocks and against 16-byte stores, the fewest K stages and more;
+logits against the oracle, tokens the first maximum of the returned logits."""
 import numpy as np
 import pytest
 
@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("kind", ["f16", "bf16"])
 @pytest.mark.parametrize("B,vocab,d", [(2, 63, 128), (16, 257, 128), (17, 642, 256), (33, 1000, 128),
-                                       (5, 64, 2048)])
+                                       (5, 64, 2048), (2, 63, 512), (16, 257, 512), (17, 642, 640),
+                                       (33, 1000, 512)])
 def test_lm_head_of_several_sequences(kind, B, vocab, d):
     w = synth.Workload(name="lmhead", seed=61, n_layers=1, d_model=d, n_heads=d // 64, d_ffn=128, vocab=vocab,
                        max_pos=8, dtype=kind, batch=B, seq_len=3, lora_rank=8, lora_alpha=16.0, n_adapters=0,
