@@ -8,6 +8,7 @@
 #include "gemm_plan.h"
 
 #include <cstdio>
+#include <cstdlib>
 #include <map>
 #include <string>
 #include <vector>
@@ -116,7 +117,28 @@ void run(int role, int M, int N, int K, int group, bool ln, size_t ws_bytes) {
 
 }  // namespace
 
-int main() {
+// the plan of one product of more than GEMV_MAX_ROWS rows: kernel, block and its
+// K elements per stage, K ranges launched, K tiles per range of the sum
+void print_plan(int M, int N, int K, size_t ws_bytes) {
+    pb::GemmParams p{};
+    p.M = M; p.N = N; p.K1 = K; p.group = N; p.ldx = p.ldw = K;
+    const pb::GemmWorkspace ws{ws_bytes ? (void*)0x40000000 : nullptr, ws_bytes};
+    const pb::TilePlan base = pb::plan_tiles(p, ws);
+    const pb::WidePlan w = pb::plan_wide(p, ws, base);
+    const char* kinds[] = {"tile", "stream", "ring", "pingpong"};
+    if (w.kind == pb::WIDE_NONE)
+        std::printf("tile %d %d 64 %d %d%s\n", base.tile, base.tile, base.splits,
+                    pb::make_split(p, ws, base.splits).kt_split, base.ragged_tail ? " ragged" : "");
+    else
+        std::printf("%s %d %d %d %d %d\n", kinds[w.kind], w.bm, w.bn, w.kind == pb::WIDE_STREAM ? w.bk : 64, w.splits,
+                    pb::make_split(p, ws, base.splits).kt_split);
+}
+
+int main(int argc, char** argv) {
+    if (argc == 5) {
+        print_plan(std::atoi(argv[1]), std::atoi(argv[2]), std::atoi(argv[3]), std::strtoull(argv[4], nullptr, 10));
+        return 0;
+    }
     for (int d : {128, 256, 384, 2048, 2176, 4096, 5120, 9216})
         for (int F : {4 * d, 4 * d + 64})
             for (int M : {1, 2, 3, 4, 5, 8, 9, 16, 31, 32, 33, 61, 64, 65, 100, 128, 129, 200, 256, 257, 333, 385, 512, 513, 700, 1000, 2000,
