@@ -63,25 +63,37 @@ def _one(d, pattern):
     return files[0]
 
 
+def _gemm_args(name):
+    """(kernel, its integer template arguments) of a GEMM kernel's mangled name."""
+    m = re.search(r"(?:\d|__)(gemm|gemm_pingpong|stream)_kernelIDF16[b_]((?:Li\d+E)+)", name)
+    return (m.group(1), [int(x) for x in re.findall(r"Li(\d+)E", m.group(2))]) if m else (None, [])
+
+
+def _gemm_role(kernel, a):
+    return a[{"gemm": 5, "gemm_pingpong": 2, "stream": 7}[kernel]]
+
+
 def kind_of(name):
     """Kernel family of a mangled kernel name (GEMM role from its template arguments)."""
     roles = {0: "gemm_qkv", 1: "gemm_o", 2: "gemm_fc1", 3: "gemm_fc2", 4: "lora_shrink"}
-    m = re.search(r"gemm_kernelIDF16b?_((?:Li\d+E)+)", name) or \
-        re.search(r"gemm_kernelIDF16_((?:Li\d+E)+)", name)
-    if m:
-        a = [int(x) for x in re.findall(r"Li(\d+)E", m.group(1))]
-        return roles.get(a[5], "gemm")
+    kernel, a = _gemm_args(name)
+    if kernel:
+        return roles.get(_gemm_role(kernel, a), "gemm")
     if "splitk_resid_ln_kernel" in name:
-        return roles[int(re.search(r"splitk_resid_ln_kernelIDF16b?_Li(\d+)E", name).group(1))] + " reduce"
+        return roles[int(re.search(r"splitk_resid_ln_kernelIDF16[b_]Li(\d+)E", name).group(1))] + " reduce"
     if "tail_reduce_kernel" in name:
-        return roles[int(re.search(r"tail_reduce_kernelIDF16b?_Li\d+ELi(\d+)E", name).group(1))] + " reduce"
+        return roles[int(re.search(r"tail_reduce_kernelIDF16[b_]Li\d+ELi(\d+)E", name).group(1))] + " reduce"
     if "splitk_reduce_kernel" in name:
-        return roles[int(re.search(r"splitk_reduce_kernelIDF16b?_Li\d+ELi(\d+)E", name).group(1))] + " reduce"
-    m = re.search(r"gemv_kernelIDF16b?_Li(\d+)E", name)
+        return roles[int(re.search(r"splitk_reduce_kernelIDF16[b_]Li\d+ELi(\d+)E", name).group(1))] + " reduce"
+    m = re.search(r"gemv_kernelIDF16[b_]Li(\d+)E", name)
     if m:  # decode steps: named by epilogue (o and fc2 share the residual one)
         return {0: "gemv_qkv", 1: "gemv_fc1", 2: "gemv_o_fc2", 3: "gemv_shrink"}[int(m.group(1))]
     if "decode_attention" in name:
         return "decode_attention"
+    if "row_shrink" in name:
+        return "lora_shrink"
+    if "split_terms" in name:  # the LM head's operand, made by a launch of its own
+        return "lm_head terms"
     for k in ("attention", "layernorm", "lm_head", "argmax", "embed", "lora_pack", "lora_merge"):
         if k in name:
             return k
@@ -186,7 +198,8 @@ def source_sha256():
 
 
 def _base(kind):
-    return kind[:-len(" reduce")] if kind and kind.endswith(" reduce") else kind
+    """The kind a launch belongs to: a reduce, or the terms before an LM head, to its product."""
+    return kind.split(" ")[0] if kind else kind
 
 
 def kernels(d, label):
@@ -203,7 +216,7 @@ def kernels(d, label):
                 float(r["TotalDurationNs"]) / 1e6, float(r["Percentage"])))
         if k:
             total[_base(k)] += float(r["TotalDurationNs"])
-            if not k.endswith(" reduce"):
+            if k == _base(k):
                 launches[k] += int(r["Calls"])
     out += ["\nAverage duration per launch by kind (a GEMM kind includes its split-K reduce):\n",
             "| kind | launches | avg us |", "|---|---|---|"]
@@ -244,7 +257,7 @@ def traffic(fetch, write, cal_fetch, cal_write, label):
         out.append("| `%s` | %s | %d | %.2f | %.2f |" % (name[:90], k, len(vals), rb / len(vals) / 1e6,
                                                         (wb / len(wv) if wv else 0.0) / 1e6))
         tot[_base(k)] += rb + (wb * len(vals) / len(wv) if wv else 0.0)
-        if not k.endswith(" reduce"):
+        if k == _base(k):
             launches[k] += len(vals)
     out += ["\nHBM bytes per launch of each kind (all its dispatches, split-K reduces included, over "
             "its launches), read by bench.py while the kernel sources keep this hash:\n",
@@ -257,15 +270,17 @@ def traffic(fetch, write, cal_fetch, cal_write, label):
 
 
 def _gemm_key(name):
-    m = re.search(r"attention_kernelIDF16b?_((?:Li\d+E)+)", name)
+    m = re.search(r"attention_kernelIDF16[b_]((?:Li\d+E)+)", name)
     if m and "decode" not in name:
         a = [int(x) for x in re.findall(r"Li(\d+)E", m.group(1))]
-        return "attention hd %d, %d queries/wave, %d key group(s)" % (a[0], a[1], a[2])
-    m = re.search(r"gemm_kernelIDF16b?_((?:Li\d+E)+)", name)
-    if m:
-        a = [int(x) for x in re.findall(r"Li(\d+)E", m.group(1))]
-        return "this library %dx%d, %d waves, %s" % (a[1], a[2], 64 * a[3] * a[4] // 64,
-                                                    {0: "qkv", 1: "o", 2: "fc1", 3: "o/fc2"}.get(a[5], "?"))
+        return "attention hd %d, %d waves of %d queries, %d key group(s)" % (a[0], a[2] * a[3], a[1], a[2])
+    kernel, a = _gemm_args(name)
+    if kernel:
+        role = {0: "qkv", 1: "o", 2: "fc1", 3: "o/fc2"}.get(_gemm_role(kernel, a), "?")
+        if kernel == "gemm_pingpong":
+            return "this library %dx256 ping-pong, 8 waves, %s" % (64 * a[1], role)
+        return "this library %dx%d%s, %d waves, %s" % (a[1], a[2], " streaming" if kernel == "stream" else "",
+                                                      a[3] * a[4], role)
     m = re.search(r"(MT\d+x\d+x\d+)", name)
     if "Cijk" in name and m:
         return "vendor library " + m.group(1)
