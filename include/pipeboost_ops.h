@@ -43,7 +43,7 @@ int pb_op_gemm(int32_t dtype, int32_t epi, const void* X, const void* W, const v
  * shrink s (x A_slot) in its adapter slot's columns of every group block
  * (zeros in the other slots' columns, so rows of different adapters, or none,
  * share the launch); W2 [N, K2] dt holds the B matrices of all slots side by
- * side.  K2 % 64 == 0, group % 64 == 0; other requirements and the workspace
+ * side.  K2 % 64 == 0, group % 256 == 0; other requirements and the workspace
  * as pb_op_gemm. */
 int pb_op_gemm_lora(int32_t dtype, int32_t epi, const void* X, const void* W, const void* bias, void* C,
                     float* R, int32_t M, int32_t N, int32_t K, const void* Z, int32_t ldz, int32_t zs,

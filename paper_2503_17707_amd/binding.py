@@ -605,9 +605,10 @@ def plan_loading(n_layers: int, alive: Sequence[bool]):
 # Arguments are torch tensors on the GPU; the call is enqueued on `stream`
 # (a torch.cuda.Stream, default: the current stream).
 
-# The wrappers cost host time that a one-token product feels (6.4 us on the GPU,
-# 7.7 us a call before): addresses go as plain integers (their argtypes are
-# void pointers) and the current stream's handle is asked for directly.
+# The wrappers cost host time that a one-token product feels (a qkv product of d
+# 2048 called in a row: 5.7 us a call, 7.8 with an address object per operand and
+# the stream looked up through its class): addresses go as plain integers (their
+# argtypes are void pointers), the current stream's handle is asked for directly.
 
 def _ptr(t):
     return None if t is None else t.data_ptr()

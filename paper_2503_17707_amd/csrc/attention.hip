@@ -265,7 +265,10 @@ void attention_kernel(const T* __restrict__ qkv, const T* __restrict__ kvsrc, in
 #pragma unroll
                 for (int r = 0; r < 4; ++r) mx = fmaxf(mx, sc[qg][jt][r]);
             mx = group4_max(mx);
-            // key kb*64 <= q_idx always holds for a computed tile, so m_new is finite
+            // m_new is finite: a wave's first tile holds a key that every query of
+            // it sees (tile 0, or with split keys, in blocks of 64 queries, any
+            // tile); a later tile past all of a wave's queries (the early waves
+            // of a 128-query block) is masked whole and changes nothing.
             // The running max is kept unless the tile exceeds it by more than
             // 8 in log2 units, so P stays below 2^8 (well inside dt) and the
             // accumulators are rescaled only when some query's max moved.
@@ -441,18 +444,22 @@ hipError_t launch_qw(const void* qkv, const void* kv, int64_t kv_ld, int64_t kv_
     const long pairs = (long)H * B;
     const long blocks128 = (long)((T_len + 127) / 128) * pairs;
     const long blocks64 = (long)((T_len + 63) / 64) * pairs;
-    // Short prompts: a block no wider than the prompt (every wave beyond it
-    // only copies; H 32, hd 64: 200 x 20 tokens 24.2 us against 36.9 with 128
-    // queries per block, 64 x 64 tokens 18.0 against 20.0).
+    // Short prompts: a block no wider than the prompt (a wave past it computes
+    // its tiles like the others and throws them away; H 32, hd 64: 200 x 20
+    // tokens 21.1 us as two waves of 16 queries, 23.0 as four, 31.9 as four of 32;
+    // 64 x 64 tokens 14.5 as four of 16 against 15.3).
     if constexpr (HD == 64)
         if (T_len <= 32) return launch_hd<T, HD, 16, 1, 2, 2>(qkv, kv, kv_ld, kv_seq, out, B, T_len, H, s);
-    // with fewer than 512 blocks of 64 queries, two wave groups split the keys
+    // with fewer than 512 blocks of 64 queries, two wave groups split the keys.
+    // At exactly 512 (us, unsplit / split) few long prompts would gain, many short
+    // ones lose more: hd 64 1 x 1000 17.1 / 13.6, 8 x 128 5.4 / 5.9; hd 128 1 x
+    // 1000 23.4 / 21.7, 2 x 500 14.3 / 15.7, 4 x 256 9.9 / 12.6, 8 x 128 7.9 / 10.9
     if (PB_ATTN_KS2 && blocks64 < 512 && T_len > BKV)
         return launch_hd<T, HD, 16, 2, 4, 2>(qkv, kv, kv_ld, kv_seq, out, B, T_len, H, s);
     // 128 queries per block when that still gives every CU two: as 4 waves of
     // 32 for head_dim 128 (fewer LDS reads per product), 8 waves of 16 for 64
-    // (more waves in flight: 48 x 77 tokens 19.3 us against 20.6, 1 x 2000
-    // 35.2 against 39.9, 16 x 250 equal)
+    // (more waves in flight: 48 x 77 tokens 16.9 us against 17.8, 1 x 2000
+    // 34.0 against 35.8, 16 x 250 18.4 against 19.5)
     if (T_len > 64 && blocks128 >= 512) {
         if constexpr (HD == 64) return launch_hd<T, HD, 16, 1, 8, 2>(qkv, kv, kv_ld, kv_seq, out, B, T_len, H, s);
         else if (PB_ATTN_QW32) return launch_hd<T, HD, 32, 1, 4, 2>(qkv, kv, kv_ld, kv_seq, out, B, T_len, H, s);

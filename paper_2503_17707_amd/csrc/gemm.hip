@@ -53,7 +53,7 @@ namespace {
 #define PB_GEMM_S64 4  // ... of the 64 x 64 tiles
 #endif
 #ifndef PB_GEMM_GEMV
-#define PB_GEMM_GEMV 1  // weight-streaming kernel for at most 8 token rows
+#define PB_GEMM_GEMV 1  // dot-product kernel for few token rows (plan_few)
 #endif
 #ifndef PB_GEMV_KW8
 #define PB_GEMV_KW8 1  // GEMV rows of K >= 4096 split over eight waves
@@ -276,7 +276,9 @@ void gemm_kernel(GemmParams p, SplitArgs sa) {
 // every wait is for all but the youngest one and a half tiles of a wave's copies.  Past the last
 // tile the copies re-read it (they land in regions nobody reads).
 //
-// Bound by the matrix units at the clock the power limit leaves; OPT-66B fc1
+// Bound by the matrix units (0.76 - 0.78 busy in counter runs at the OPT-66B
+// shapes, the plain ring 0.60) at the clock the power limit leaves (1.70 GHz,
+// 1.95 there); OPT-66B fc1
 // (M 4096, N 36864, K 9216, f16) 2235 -> 2000 us (1245 -> 1395 TFLOP/s, the
 // vendor library 1406), M 2000, N 20480, K 5120 416 -> 361 us.  The K order of
 // every output is that of the plain loop (bit-identical results).

@@ -172,8 +172,9 @@ TileGeometry tile_geometry(const GemmParams& p, const GemmWorkspace& wsp, int sp
 }
 
 // Tile shape and K split of a launch, from a cost model: a block's time is
-// its MFMA work at the rate one CU reaches with that tile (measured: 256 x 256
-// ~4.5 TFLOP/s, 128 x 128 ~2.6), blocks run in rounds of 256 (one per CU), and
+// its MFMA work at the rate of one CU with that tile (256 x 256 4.5 TFLOP/s, 128 x
+// 128 2.6: measured with a plain ring in both; the 256 x 256 kernel now reaches
+// 5.4, but another rate would move K ranges and with them the bits of results), blocks run in rounds of 256 (one per CU), and
 // a split adds its fp32 partials (written, then read by the reduce) at
 // ~4 TB/s.  Splits keep >= PB_GEMM_MIN_KT K tiles each and fit the workspace.
 struct TilePlan {
@@ -293,7 +294,9 @@ inline double tile_time(const GemmParams& p, int bm, int bn, int splits) {
     const double fixed = bn == 256 ? 6e-6 : 4e-6;
     double t = (double)((blocks + 255) / 256) * (double)((p.K1 / BK + splits - 1) / splits) * per_kt;
     // eight K ranges a multiple of 4 KB apart read the same HBM channels (N
-    // 4096, K 16384, 100 rows: 51.8 us, six ranges 40.1)
+    // 4096 in 128 x 128 tiles, one round of 256 blocks: K 16384 in eight ranges 49 us
+    // for 50 rows and 53 for 100, this model without the term 38 and 39; in six
+    // 38 and 42; K 12288, 3 KB apart, in eight 28 and 30)
     if (splits == 8 && (p.K1 / 8 * 2) % 4096 == 0) t *= 1.5;
     t = std::max(t, (double)p.N * p.K1 * 2 / 4.8e12);  // cold weights in 128-byte row pieces
     return fixed + t + split_cost(p, splits);
@@ -320,13 +323,13 @@ inline int wide_row_stage(const GemmParams& p, int bn, int splits) {
 }
 
 // `base`: plan_tiles' choice for the same launch, kept unless another shape is
-// predicted 5% (streaming) or 8% (tiles) faster.  Every other shape sums K in the same ranges as the
-// base, added in the same order (tiles: the same split; the streaming kernel:
+// predicted 5% (streaming) or 8% (tiles) faster; up to GEMV_MAX_ROWS rows plan_few
+// decides.  Every other shape sums K in the same ranges as the base, added in the same order (tiles: the same split; the streaming kernel:
 // the same split, or one block that closes a running sum at each range's end),
 // so the result does not depend on the shape chosen, bit for bit; ragged-round
 // plans, whose ranges differ from tile to tile, stay.  Measured gains over the
 // base (us): M 24, N 16384, K 4096 38 -> 27 (stream), M 200, N 6144, K 2048 20.1
-// -> 15.9 (stream 128 x 64), M 333, N 16384, K 4096 77 -> 59 (192 x 128), M 333,
+// -> 15.9 (stream 128 x 64), M 333, N 16384, K 4096 77 -> 59 (192 x 256), M 333,
 // N 5120, K 20480 112 -> 91 (192 x 256), M 700, N 15360, K 5120 152 -> 110 (192
 // x 256).
 WidePlan plan_wide(const GemmParams& p, const GemmWorkspace& wsp, const TilePlan& base) {

@@ -53,8 +53,8 @@ struct GemmWorkspace {
     size_t bytes;
 };
 
-// Products with at most this many token rows may stream the weights with the
-// GEMV kernel (decode steps) instead of MFMA tiles.
+// Products with at most this many token rows run as the GEMV (decode steps) or
+// the streaming kernel, whichever is predicted faster, never as MFMA tiles.
 constexpr int GEMV_MAX_ROWS = 8;
 
 // role: 0 qkv, 1 o, 2 fc1, 3 fc2, 4 shrink (selects the instantiation; each
