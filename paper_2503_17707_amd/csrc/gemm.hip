@@ -913,11 +913,23 @@ hipError_t launch_wide(const GemmParams& p, const GemmWorkspace& wsp, const Wide
     return launch_stream_cfg<T, EPI, 32, 64, 1, 4, 128, 3, ROLE>(p, wsp, w, s);
 }
 
+template <typename T, int EPI>
+hipError_t launch_gemv(const GemmParams& p, hipStream_t s);
+
+// Few rows: the GEMV unless the streaming kernel is planned (never for the LoRA
+// shrink, whose epilogue it does not know); more: tiles or the streaming kernel.
 template <typename T, int EPI, int ROLE>
-hipError_t launch_tiles(const GemmParams& p, const GemmWorkspace& wsp, hipStream_t s) {
+hipError_t launch_role(const GemmParams& p, const GemmWorkspace& wsp, hipStream_t s) {
+    if (PB_GEMM_GEMV && p.M <= GEMV_MAX_ROWS) {
+        if constexpr (ROLE != 4) {
+            const WidePlan w = plan_few(p, wsp);
+            if (w.kind != WIDE_NONE) return launch_wide<T, EPI, ROLE>(p, wsp, w, s);
+        }
+        return launch_gemv<T, EPI>(p, s);
+    }
     const TilePlan tp = plan_for_role(ROLE, p, wsp);
     if constexpr (ROLE != 4) {
-        const WidePlan w = p.M <= GEMV_MAX_ROWS ? plan_few(p, wsp) : plan_wide(p, wsp, tp);
+        const WidePlan w = plan_wide(p, wsp, tp);
         if (w.kind != WIDE_NONE) return launch_wide<T, EPI, ROLE>(p, wsp, w, s);
     }
     if constexpr (ROLE == 4) {
@@ -934,11 +946,11 @@ hipError_t launch_tiles(const GemmParams& p, const GemmWorkspace& wsp, hipStream
 template <typename T>
 hipError_t launch_typed(int role, const GemmParams& p, const GemmWorkspace& wsp, hipStream_t s) {
     switch (role) {
-        case 0: return launch_tiles<T, EPI_QKV, 0>(p, wsp, s);
-        case 1: return launch_tiles<T, EPI_RESID, 1>(p, wsp, s);
-        case 2: return launch_tiles<T, EPI_RELU, 2>(p, wsp, s);
-        case 3: return launch_tiles<T, EPI_RESID, 3>(p, wsp, s);
-        case 4: return launch_tiles<T, EPI_SHRINK, 4>(p, wsp, s);
+        case 0: return launch_role<T, EPI_QKV, 0>(p, wsp, s);
+        case 1: return launch_role<T, EPI_RESID, 1>(p, wsp, s);
+        case 2: return launch_role<T, EPI_RELU, 2>(p, wsp, s);
+        case 3: return launch_role<T, EPI_RESID, 3>(p, wsp, s);
+        case 4: return launch_role<T, EPI_SHRINK, 4>(p, wsp, s);
         default: break;
     }
     return hipErrorInvalidValue;
@@ -1063,18 +1075,6 @@ hipError_t launch_gemv(const GemmParams& p, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_gemv_typed(int role, const GemmParams& p, hipStream_t s) {
-    switch (role) {
-        case 0: return launch_gemv<T, EPI_QKV>(p, s);
-        case 1: case 3: return launch_gemv<T, EPI_RESID>(p, s);
-        case 2: return launch_gemv<T, EPI_RELU>(p, s);
-        case 4: return launch_gemv<T, EPI_SHRINK>(p, s);
-        default: break;
-    }
-    return hipErrorInvalidValue;
-}
-
 }  // namespace
 
 hipError_t launch_gemm(int dtype, int role, int epi, const GemmParams& p, const GemmWorkspace& wsp,
@@ -1087,11 +1087,6 @@ hipError_t launch_gemm(int dtype, int role, int epi, const GemmParams& p, const 
         return hipErrorInvalidValue;
     const int expect[5] = {EPI_QKV, EPI_RESID, EPI_RELU, EPI_RESID, EPI_SHRINK};
     if (role < 0 || role > 4 || expect[role] != epi) return hipErrorInvalidValue;
-    // few rows: the GEMV unless the streaming kernel is planned (never for the
-    // LoRA shrink, whose epilogue it does not know)
-    const bool gemv = p.M <= GEMV_MAX_ROWS && (role == 4 || plan_few(p, wsp).kind == WIDE_NONE);
-    if (PB_GEMM_GEMV && gemv)
-        return dtype == 1 ? launch_gemv_typed<_Float16>(role, p, s) : launch_gemv_typed<__bf16>(role, p, s);
     if (dtype == 1) return launch_typed<_Float16>(role, p, wsp, s);
     return launch_typed<__bf16>(role, p, wsp, s);
 }

@@ -384,7 +384,8 @@ inline double gemv_time(const GemmParams& p) {
 inline double few_stream_time(const GemmParams& p, int bn, int splits) {
     const long blocks = (long)(p.N / bn) * splits, per_cu = (blocks + 255) / 256;
     const double copy = per_cu * ((double)p.K1 / splits) * (32 + bn) * 2 / 75e9;
-    const double hbm = (double)p.N * p.K1 * 2 / 7.2e12 / std::pow(std::min(1.0, (double)blocks / 256), 0.4);
+    double hbm = (double)p.N * p.K1 * 2 / 7.2e12;
+    if (blocks < 256) hbm /= std::pow((double)blocks / 256, 0.4);
     const double t = std::max(copy, hbm) + 0.5 * std::min(copy, hbm);
     return 3.7e-6 + (bn == 32 ? 1.03 * t : t) +
            (splits > 1 ? 2.0 * p.M * p.N * 4 * splits / 8e12 + 3e-6 : split_cost(p, 1));
