@@ -459,10 +459,14 @@ hipError_t launch_qw(const void* qkv, const void* kv, int64_t kv_ld, int64_t kv_
     // 128 queries per block when that still gives every CU two: as 4 waves of
     // 32 for head_dim 128 (fewer LDS reads per product), 8 waves of 16 for 64
     // (more waves in flight: 48 x 77 tokens 16.9 us against 17.8, 1 x 2000
-    // 34.0 against 35.8, 16 x 250 18.4 against 19.5)
+    // 34.0 against 35.8, 16 x 250 18.4 against 19.5; not for long prompts with
+    // 1024 blocks and more, where 4 waves of 32 are 0-3% faster: 2 x 2048 51.7
+    // against 54.2)
     if (T_len > 64 && blocks128 >= 512) {
-        if constexpr (HD == 64) return launch_hd<T, HD, 16, 1, 8, 2>(qkv, kv, kv_ld, kv_seq, out, B, T_len, H, s);
-        else if (PB_ATTN_QW32) return launch_hd<T, HD, 32, 1, 4, 2>(qkv, kv, kv_ld, kv_seq, out, B, T_len, H, s);
+        if constexpr (HD == 64)
+            if (T_len <= 512 || blocks128 < 1024)
+                return launch_hd<T, HD, 16, 1, 8, 2>(qkv, kv, kv_ld, kv_seq, out, B, T_len, H, s);
+        if (PB_ATTN_QW32) return launch_hd<T, HD, 32, 1, 4, 2>(qkv, kv, kv_ld, kv_seq, out, B, T_len, H, s);
     }
     return launch_hd<T, HD, 16, 1, 4, 2>(qkv, kv, kv_ld, kv_seq, out, B, T_len, H, s);
 }
