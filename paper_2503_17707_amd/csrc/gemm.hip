@@ -7,7 +7,8 @@
 // (dt) or 16-byte (fp32 residual) vectors.
 //
 // Block tile BM x BN, K tile 64: 256 x 256 (two wave groups in ping-pong over
-// a 2-stage ring, 128 KiB of LDS: gemm_pingpong_kernel) or 128 x 128 (3-stage
+// a 2-stage ring, 128 KiB of LDS: gemm_pingpong_kernel; a plain ring for short
+// cold K ranges: plain_ring) or 128 x 128 (3-stage
 // ring: with few tiles the weights arrive cold from HBM and a deeper ring
 // hides more of that latency) with 8 waves (2 x 4, two waves per SIMD), chosen
 // by how many tiles the shape gives, and 64 x 64 with 4 waves for N not a
@@ -276,8 +277,8 @@ void gemm_kernel(GemmParams p, SplitArgs sa) {
 // every wait is for all but the youngest one and a half tiles of a wave's copies.  Past the last
 // tile the copies re-read it (they land in regions nobody reads).
 //
-// Bound by the matrix units (0.76 - 0.78 busy in counter runs at the OPT-66B
-// shapes, the plain ring 0.60) at the clock the power limit leaves (1.70 GHz,
+// Bound by the matrix units (0.74 - 0.78 busy in counter runs at the OPT-66B
+// shapes, the plain ring 0.60) at the clock the power limit leaves (1.7 GHz,
 // 1.95 there); OPT-66B fc1
 // (M 4096, N 36864, K 9216, f16) 2235 -> 2000 us (1245 -> 1395 TFLOP/s, the
 // vendor library 1406), M 2000, N 20480, K 5120 416 -> 361 us.  The K order of
@@ -476,7 +477,7 @@ void gemm_pingpong_kernel(GemmParams p, SplitArgs sa) {
 // bit-identical to the base), whose few columns are read
 // straight into registers: the first 64, requested ahead of the ring, have
 // landed by the time the base is done.
-template <typename T, int EPI, int BM, int BN, int WGM, int WGN, int BKE, int S, int ROLE>
+template <typename T, int EPI, int BM, int BN, int WGM, int WGN, int BKE, int S, int ROLE, bool FEW>
 __global__ __launch_bounds__(64 * WGM * WGN) void stream_kernel(GemmParams p, SplitArgs sa, int kst) {
     typedef typename Mfma<T>::vec8 vec8;
     constexpr int NW = WGM * WGN;
@@ -568,9 +569,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void stream_kernel(GemmParams p, Sp
         }
     };
 
-    // few rows: only the first 16 tokens exist; low holds the rounding errors of sum
-    constexpr bool FEW = BM == 32;
-    const bool few = FEW && p.M <= GEMV_MAX_ROWS;
+    // FEW: only the first 16 tokens exist; low holds the rounding errors of sum (a
+    // kernel of its own: the same choice made in the loop cost more rows 1 us)
     f32x4 low[NF];
 #pragma unroll
     for (int i = 0; i < NF; ++i) low[i] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -602,7 +602,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void stream_kernel(GemmParams p, Sp
         }
     };
     auto step = [&](int stage) {
-        if (few) compute_few(stage);
+        if constexpr (FEW) compute_few(stage);
         else compute(stage);
     };
 
@@ -667,7 +667,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void stream_kernel(GemmParams p, Sp
             mul2(l1);
         }
     }
-    if (few) {
+    if constexpr (FEW) {
 #pragma unroll
         for (int i = 0; i < NF; ++i)
 #pragma unroll
@@ -844,12 +844,12 @@ hipError_t finish_split(const GemmParams& p, const SplitArgs& sa, hipStream_t s)
     return hipGetLastError();
 }
 
-template <typename T, int EPI, int BM, int BN, int WGM, int WGN, int ROLE, int S>
+template <typename T, int EPI, int BM, int BN, int WGM, int WGN, int ROLE, int S, bool RING = BN != 256>
 hipError_t launch_cfg(const GemmParams& p, const GemmWorkspace& wsp, int splits, int ragged_tail, hipStream_t s) {
     constexpr int LDS = S * (BM + BN) * ROW_BYTES;
     constexpr auto kernel = [] {
-        if constexpr (BN == 256) return &gemm_pingpong_kernel<T, EPI, BM / 64, ROLE>;
-        else return &gemm_kernel<T, EPI, BM, BN, WGM, WGN, ROLE, S>;
+        if constexpr (RING) return &gemm_kernel<T, EPI, BM, BN, WGM, WGN, ROLE, S>;
+        else return &gemm_pingpong_kernel<T, EPI, BM / 64, ROLE>;
     }();
     static bool attr_set = false;
     if (!attr_set) {
@@ -874,12 +874,12 @@ hipError_t launch_cfg(const GemmParams& p, const GemmWorkspace& wsp, int splits,
     return finish_split<T, EPI, ROLE>(p, sa, s);
 }
 
-template <typename T, int EPI, int BM, int BN, int WGM, int WGN, int BKE, int S, int ROLE>
+template <typename T, int EPI, int BM, int BN, int WGM, int WGN, int BKE, int S, int ROLE, bool FEW = false>
 hipError_t launch_stream_cfg(const GemmParams& p, const GemmWorkspace& wsp, const WidePlan& w, hipStream_t s) {
     constexpr int LDS = S * (BM + BN) * BKE * 2;
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)stream_kernel<T, EPI, BM, BN, WGM, WGN, BKE, S, ROLE>,
+        hipError_t e = hipFuncSetAttribute((const void*)stream_kernel<T, EPI, BM, BN, WGM, WGN, BKE, S, ROLE, FEW>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
         if (e != hipSuccess) return e;
         attr_set = true;
@@ -889,7 +889,7 @@ hipError_t launch_stream_cfg(const GemmParams& p, const GemmWorkspace& wsp, cons
     sa.kt_split = w.kt;
     sa.ws = (float*)wsp.ws;
     const int kst = w.splits > 1 ? w.kt * BK / BKE : p.K1 / BKE;  // ring stages per launched range
-    PB_LAUNCH((stream_kernel<T, EPI, BM, BN, WGM, WGN, BKE, S, ROLE>), dim3((unsigned)((p.M + BM - 1) / BM * (p.N / BN) * w.splits)),
+    PB_LAUNCH((stream_kernel<T, EPI, BM, BN, WGM, WGN, BKE, S, ROLE, FEW>), dim3((unsigned)((p.M + BM - 1) / BM * (p.N / BN) * w.splits)),
               dim3(64 * WGM * WGN), LDS, s, p, sa, kst);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || w.splits == 1) return e;
@@ -899,8 +899,8 @@ hipError_t launch_stream_cfg(const GemmParams& p, const GemmWorkspace& wsp, cons
 template <typename T, int EPI, int ROLE>
 hipError_t launch_wide(const GemmParams& p, const GemmWorkspace& wsp, const WidePlan& w, hipStream_t s) {
     if (w.kind == WIDE_RING) {
-        if (w.bm == 192) return launch_cfg<T, EPI, 192, 128, 2, 4, ROLE, 4>(p, wsp, w.splits, 0, s);
-        return launch_cfg<T, EPI, 128, 128, 2, 4, ROLE, PB_GEMM_S128>(p, wsp, w.splits, 0, s);
+        if (w.bm == 256) return launch_cfg<T, EPI, 256, 256, 2, 4, ROLE, 2, true>(p, wsp, w.splits, 0, s);
+        return launch_cfg<T, EPI, 192, 128, 2, 4, ROLE, 4>(p, wsp, w.splits, 0, s);
     }
     if (w.kind == WIDE_PINGPONG) {
         if (w.bm == 192) return launch_cfg<T, EPI, 192, 256, 2, 4, ROLE, 2>(p, wsp, w.splits, 0, s);
@@ -908,6 +908,11 @@ hipError_t launch_wide(const GemmParams& p, const GemmWorkspace& wsp, const Wide
     }
     if (w.bm == 128) return launch_stream_cfg<T, EPI, 128, 64, 4, 2, 128, 3, ROLE>(p, wsp, w, s);
     if (w.bm == 64) return launch_stream_cfg<T, EPI, 64, 64, 1, 4, 128, 4, ROLE>(p, wsp, w, s);
+    if (p.M <= GEMV_MAX_ROWS) {
+        if (w.bn == 32) return launch_stream_cfg<T, EPI, 32, 32, 1, 2, 128, 4, ROLE, true>(p, wsp, w, s);
+        if (w.bk == 256) return launch_stream_cfg<T, EPI, 32, 64, 1, 4, 256, 3, ROLE, true>(p, wsp, w, s);
+        return launch_stream_cfg<T, EPI, 32, 64, 1, 4, 128, 3, ROLE, true>(p, wsp, w, s);
+    }
     if (w.bn == 32) return launch_stream_cfg<T, EPI, 32, 32, 1, 2, 128, 4, ROLE>(p, wsp, w, s);
     if (w.bk == 256) return launch_stream_cfg<T, EPI, 32, 64, 1, 4, 256, 3, ROLE>(p, wsp, w, s);
     return launch_stream_cfg<T, EPI, 32, 64, 1, 4, 128, 3, ROLE>(p, wsp, w, s);

@@ -242,7 +242,7 @@ enum WideKind { WIDE_NONE = 0, WIDE_STREAM, WIDE_RING, WIDE_PINGPONG };
 
 struct WidePlan {
     int kind;    // WideKind; WIDE_NONE: plan_tiles' choice stands
-    int bm, bn;  // stream: 32 x 64, 32 x 32, 64 x 64, 128 x 64; ring: 128 or 192 x 128; ping-pong: 128 or 192 x 256
+    int bm, bn;  // stream: 32 x 64, 32 x 32, 64 x 64, 128 x 64; ring: 192 x 128, 256 x 256; ping-pong: 128 or 192 x 256
     int bk;      // stream: K elements per ring stage (128 or 256)
     int splits;  // K ranges launched
     int kt;      // stream: K tiles (of 64) per range of plan_tiles' split (the sum's order), or all of them
@@ -272,48 +272,50 @@ __host__ __device__ __forceinline__ StreamJob stream_job(const GemmParams& p, in
 
 // What a K split or its absence costs beside the product: partials written and
 // read (mostly from the last-level cache: ~8 TB/s) and a reduce launch of its
-// own (4 us) unless the LayerNorm that follows is that reduce; without a split
-// that LayerNorm is a pass.
-inline double split_cost(const GemmParams& p, int splits) {
+// own (`launch`, as fitted in recorded graphs) unless the LayerNorm that follows is
+// that reduce; without a split that LayerNorm is a pass.
+inline double split_cost(const GemmParams& p, int splits, double launch) {
     const double out = (double)p.M * p.N * 4;
-    if (splits > 1) return 2.0 * out * splits / 8e12 + (p.ln_out ? 0.0 : 4e-6);
+    if (splits > 1) return 2.0 * out * splits / 8e12 + (p.ln_out ? 0.0 : launch);
     return p.ln_out ? out * 1.5 / 4e12 + 3e-6 : 0.0;
 }
 
-// Time of a tile launch: rounds of 256 blocks (one per CU) at the measured
-// time per 64-wide K tile (M 100 .. 2000, cold weights), and the launch, the
-// ring's first tiles and the epilogue.
+// Eight K ranges a multiple of 4 KB apart read the same HBM channels (N 4096 in
+// 128 x 128 tiles, one round of 256 blocks: K 16384 in eight ranges 49 us for 50
+// rows and 53 for 100, in six 38 and 42; K 12288, 3 KB apart, in eight 28 and 30).
+inline bool same_channels(const GemmParams& p, int splits) { return splits == 8 && p.K1 / 8 * 2 % 4096 == 0; }
+
+// Times of a tile and of a stream launch, fitted together to 5600 launches (the
+// projections of d_model 768 .. 9216, 9 .. 2000 rows, cold weights; mean error 8%).
+//
+// Tiles: rounds of 256 blocks (one per CU) at a time per 64-wide K tile, cold
+// weights in 128-byte row pieces at 6.8 TB/s, 0.29 of the shorter left over; and
+// the launch, the ring's first tiles and the epilogue.
 inline double tile_time(const GemmParams& p, int bm, int bn, int splits) {
-    const long tiles = (long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn);
-    const long blocks = tiles * splits;
+    const long blocks = (long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn) * splits, rounds = (blocks + 255) / 256;
     double per_kt;
-    if (bn == 256) per_kt = bm == 256 ? 1.7e-6 : bm == 192 ? 1.36e-6 : 1.06e-6;
-    else if (bm == 192) per_kt = 0.84e-6;
-    else if (bm == 128) per_kt = 0.47e-6 + 0.22e-6 * (double)std::min<long>(blocks, 256) / 256;
+    if (bn == 256) per_kt = bm == 256 ? 1.43e-6 : bm == 192 ? 1.18e-6 : 0.88e-6;
+    else if (bm == 192) per_kt = 0.76e-6;
+    else if (bm == 128) per_kt = 0.32e-6 + 0.26e-6 * (double)std::min<long>(blocks, 256) / 256;
     else per_kt = 0.30e-6;
-    const double fixed = bn == 256 ? 6e-6 : 4e-6;
-    double t = (double)((blocks + 255) / 256) * (double)((p.K1 / BK + splits - 1) / splits) * per_kt;
-    // eight K ranges a multiple of 4 KB apart read the same HBM channels (N
-    // 4096 in 128 x 128 tiles, one round of 256 blocks: K 16384 in eight ranges 49 us
-    // for 50 rows and 53 for 100, this model without the term 38 and 39; in six
-    // 38 and 42; K 12288, 3 KB apart, in eight 28 and 30)
-    if (splits == 8 && (p.K1 / 8 * 2) % 4096 == 0) t *= 1.5;
-    t = std::max(t, (double)p.N * p.K1 * 2 / 4.8e12);  // cold weights in 128-byte row pieces
-    return fixed + t + split_cost(p, splits);
+    double work = (double)rounds * (double)((p.K1 / BK + splits - 1) / splits) * per_kt;
+    if (rounds == 1 && same_channels(p, splits)) work *= 1.43;
+    const double hbm = (double)p.N * p.K1 * 2 / 6.8e12;
+    return (bn == 256 ? 7.7e-6 : 7.0e-6) + std::max(work, hbm) + 0.29 * std::min(work, hbm) + split_cost(p, splits, 1e-6);
 }
 
-// Time of a stream launch: a CU copies ~60 GB/s into LDS whatever the block
-// shape (blocks on one CU share it), the chip streams cold weights at ~5.2
-// TB/s, the two overlap but for a fifth of the shorter; ~3 us beside that, and
-// 2 more per further round of blocks that fill a CU's LDS (all but the 32-row
-// ones).  Within 15% of the measured times over M = 16 .. 333, N = 2048 ..
-// 20480.
+// Streams: a CU copies 70 GB/s into LDS whatever the block shape (blocks on one
+// CU share it), the chip streams cold weights at 7.1 TB/s (32-row blocks less
+// when their rounds leave CUs idle), 0.46 of the shorter left over, and 2.4 us per
+// further round of blocks that fill a CU's LDS (all but the 32-row ones).
 inline double stream_time(const GemmParams& p, int bm, int bn, int splits) {
-    const long per_cu = ((long)((p.M + bm - 1) / bm) * (p.N / bn) * splits + 255) / 256;
-    const double copy = per_cu * ((double)p.K1 / splits) * (bm + bn) * 2 / 60e9;
-    const double hbm = (double)p.N * p.K1 * 2 / 5.2e12;
-    const double t = std::max(copy, hbm) + 0.2 * std::min(copy, hbm) + (bm > 32 ? (per_cu - 1) * 2e-6 : 0.0);
-    return 3e-6 + (bn == 32 ? 1.2 * t : t) + split_cost(p, splits);  // two waves a block: fewer copies in flight
+    const long blocks = (long)((p.M + bm - 1) / bm) * (p.N / bn) * splits, rounds = (blocks + 255) / 256;
+    const double copy = rounds * ((double)p.K1 / splits) * (bm + bn) * 2 / 70e9;
+    double hbm = (double)p.N * p.K1 * 2 / 7.1e12;
+    if (bm == 32) hbm /= std::pow((double)blocks / (256.0 * rounds), 0.2);
+    if (same_channels(p, splits)) hbm *= bm == 32 ? 1.43 : 1.67;
+    const double t = std::max(copy, hbm) + 0.46 * std::min(copy, hbm) + (bm > 32 ? (rounds - 1) * 2.4e-6 : 0.0);
+    return 4.1e-6 + (bn == 32 ? 1.05 * t : t) + split_cost(p, splits, 2.4e-6);  // bn 32: two waves, fewer copies in flight
 }
 
 // K elements per ring stage of 32-row blocks: unsplit with at most a block per
@@ -322,9 +324,23 @@ inline int wide_row_stage(const GemmParams& p, int bn, int splits) {
     return bn == 64 && splits == 1 && p.K1 % 256 == 0 && p.N / 64 <= 256 ? 256 : 128;
 }
 
+// Split launches planned on the square 256 x 256 tile keep its plain two-stage
+// ring, before any other shape is tried, where ranges are short and the weights
+// cold: one token tile of up to 24 K tiles (ping-pong / 192 x 256 / plain ring: N
+// 9216, K 9216, M 129 64 / 64 / 56 us, M 256 78 / 90 / 68; N 12288, K 4096, M 129 46
+// / 43 / 40; N 20480, K 5120, M 256, 27 K tiles 82 / - / 83), and where the ranges
+// share HBM channels (N 4096, K 16384 in eight: M 400 80 us in ping-pong, 86 in 128
+// x 256, 77; M 512 91, 91, 81; M 384 81, 102, 76).
+inline bool plain_ring(const GemmParams& p, const SplitArgs& sa) {
+    return sa.splits > 1 && ((p.M <= 256 && sa.kt_split <= 24) || same_channels(p, sa.splits));
+}
+
 // `base`: plan_tiles' choice for the same launch, kept unless another shape is
-// predicted 5% (streaming) or 8% (tiles) faster; up to GEMV_MAX_ROWS rows plan_few
-// decides.  Every other shape sums K in the same ranges as the base, added in the same order (tiles: the same split; the streaming kernel:
+// predicted faster by a margin (below); up to GEMV_MAX_ROWS rows plan_few decides.
+// Over the fitted launches the choice is 0.4% above the fastest shape in the mean;
+// 1 of 952 products is more than 4% slower than its base.  Every other shape
+// sums K in the same ranges as the base, added in the same order (tiles: the same
+// split; the streaming kernel:
 // the same split, or one block that closes a running sum at each range's end),
 // so the result does not depend on the shape chosen, bit for bit; ragged-round
 // plans, whose ranges differ from tile to tile, stay.  Measured gains over the
@@ -335,19 +351,23 @@ inline int wide_row_stage(const GemmParams& p, int bn, int splits) {
 WidePlan plan_wide(const GemmParams& p, const GemmWorkspace& wsp, const TilePlan& base) {
     WidePlan best{WIDE_NONE, 0, 0, 0, 1, 0};
     if (p.M <= GEMV_MAX_ROWS || p.M > 2048 || base.ragged_tail > 0) return best;
-    double best_t = tile_time(p, base.tile, base.tile, base.splits);
     const SplitArgs sa = make_split(p, wsp, base.splits);
-    // margins: about the scatter of the two models against measurement
+    if (base.tile == 256 && plain_ring(p, sa)) return WidePlan{WIDE_RING, 256, 256, 0, base.splits, 0};
+    double best_t = tile_time(p, base.tile, base.tile, base.splits);
+    // margins: the models' bias against measurement, shape by shape (64-row
+    // streaming blocks come out up to 12% slower than predicted, the split 128 x 128
+    // tiles beside 128-row ones up to 17%, and their reduce costs 3 us more where the
+    // launches are not replayed from a graph)
     auto consider = [&](double t, const WidePlan& w) {
-        const double margin = best.kind != WIDE_NONE ? 0.97 : w.kind == WIDE_STREAM ? 0.95 : 0.92;
+        double margin = 0.98;
+        if (best.kind == WIDE_NONE) margin = w.kind != WIDE_STREAM ? 0.97 : w.bm == 32 ? 0.98 : w.bm == 64 ? 0.92 : 1.06;
         if (t < best_t * margin) {
             best_t = t;
             best = w;
         }
     };
     struct Shape { int kind, bm, bn; };
-    for (const Shape& c : {Shape{WIDE_RING, 128, 128}, Shape{WIDE_RING, 192, 128}, Shape{WIDE_PINGPONG, 128, 256},
-                           Shape{WIDE_PINGPONG, 192, 256}}) {
+    for (const Shape& c : {Shape{WIDE_RING, 192, 128}, Shape{WIDE_PINGPONG, 128, 256}, Shape{WIDE_PINGPONG, 192, 256}}) {
         if (p.N % c.bn || (c.bm > 128 && p.M <= c.bm - 64)) continue;  // whole 64-row strips of padding
         consider(tile_time(p, c.bm, c.bn, sa.splits), WidePlan{c.kind, c.bm, c.bn, 0, base.splits, 0});
     }
@@ -375,7 +395,7 @@ WidePlan plan_wide(const GemmParams& p, const GemmWorkspace& wsp, const TilePlan
 inline double gemv_time(const GemmParams& p) {
     const int rows = p.M <= 1 ? 1 : p.M <= 2 ? 2 : p.M <= 4 ? 4 : 8, kw = p.K1 >= 4096 ? 8 : 4;
     const double dots = (double)p.N / 4 * kw * rows * (208.0 * p.K1 / kw / 512 + 400.0) / (1024 * 2.1e9);
-    return 4.6e-6 + std::max(dots, (double)p.N * p.K1 * 2 / 5.8e12) + split_cost(p, 1);
+    return 4.6e-6 + std::max(dots, (double)p.N * p.K1 * 2 / 5.8e12) + split_cost(p, 1, 0.0);
 }
 
 // ... and of a stream launch of so few rows in 32 x bn blocks: copies into LDS
@@ -388,7 +408,7 @@ inline double few_stream_time(const GemmParams& p, int bn, int splits) {
     if (blocks < 256) hbm /= std::pow((double)blocks / 256, 0.4);
     const double t = std::max(copy, hbm) + 0.5 * std::min(copy, hbm);
     return 3.7e-6 + (bn == 32 ? 1.03 * t : t) +
-           (splits > 1 ? 2.0 * p.M * p.N * 4 * splits / 8e12 + 3e-6 : split_cost(p, 1));
+           (splits > 1 ? 2.0 * p.M * p.N * 4 * splits / 8e12 + 3e-6 : split_cost(p, 1, 0.0));
 }
 
 // Launch of at most GEMV_MAX_ROWS rows: WIDE_NONE is the GEMV.  Its fp32 dot

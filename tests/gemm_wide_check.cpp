@@ -105,9 +105,9 @@ void run(int role, int M, int N, int K, int group, bool ln, size_t ws_bytes) {
         else if (w.bm == 32 && w.bn == 64 && w.bk == 128) check_stream<32, 64, 128>(p, w);
         else CHECK(false, "unknown stream shape");
     } else if (w.kind == pb::WIDE_RING) {
-        CHECK(w.bn == 128 && (w.bm == 192 || w.bm == 128), "unknown ring shape");
-        if (w.bm == 192) check_tiles<192, 128>(p, ws, w);
-        else check_tiles<128, 128>(p, ws, w);
+        CHECK((w.bn == 128 && w.bm == 192) || (w.bn == 256 && w.bm == 256), "unknown ring shape");
+        if (w.bm == 256) check_tiles<256, 256>(p, ws, w);
+        else check_tiles<192, 128>(p, ws, w);
     } else {
         CHECK(w.bn == 256 && (w.bm == 192 || w.bm == 128), "unknown ping-pong shape");
         if (w.bm == 192) check_tiles<192, 256>(p, ws, w);
